@@ -6,6 +6,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdarg>
@@ -276,6 +277,11 @@ struct lbm_ctx {
     int tb_threads = 512;
     int tb_rows = 16;
     int device = 0;  // the device current at creation (the static scratch's copy)
+    // the deep pass of a small single domain (lbm_deep.h): its tiles and the most
+    // cycles per launch, 0 where it does not pay and once the caller has chosen a
+    // pass or a tile
+    DeepPlan deep{1, 1};
+    int deep_cycles = 0;
 };
 
 namespace {
@@ -436,6 +442,19 @@ hipError_t checkpoint(lbm_ctx *c) {
 }  // namespace
 
 namespace {
+
+// Cycles of the next deep pass of a call with n cycles left (0: another pass):
+// passes of equal length, none over a checkpoint. Below three cycles the launch
+// and the ring of a larger domain cost more than the other passes (450^2 cavity,
+// one step per call: 20 us against 16; 20 x 500: 15 and 15).
+int64_t deep_pass_cycles(const lbm_ctx *c, int64_t n) {
+    if (c->deep_cycles <= 0) return 0;
+    const lbm_desc &d = c->dom[0].desc;
+    if (c->rec_valid && d.ckpt_every > 0) n = std::min<int64_t>(n, d.ckpt_every - c->t % d.ckpt_every);
+    if (n < 3 && (int64_t)d.nx * d.ny > 65536) return 0;
+    const int64_t passes = (n + c->deep_cycles - 1) / c->deep_cycles;
+    return (n + passes - 1) / passes;
+}
 
 // cycles advanced by one kernel node of the step graph
 int graph_node_steps(const lbm_ctx *c) { return c->tblock; }
@@ -635,6 +654,7 @@ int lbm_create(const lbm_desc *d, const float *phi, const float *kappa, void *wo
     // (measured 86 against 75 GLUPS for 16 rows at 1024^2)
     if (d->thermal.enabled) c->tb_rows = 8;
     if (d->storage == LBM_FP16_DEV) c->sched = Schedule{64, 2, 2, 1};
+    if (buffer_below_4gib(L)) (void)deep_plan(D.dom, &c->deep, &c->deep_cycles);
     hipError_t e = init_domain(D, 0, phi, kappa, c->stream);
     if (e != hipSuccess) {
         rc = device_fail(nullptr, e, "initialisation");
@@ -662,6 +682,19 @@ int lbm_step(lbm_ctx *c, int64_t n) {
     // lbm_reduce's residual; graph replays never end a call.
     while (n > 0) {
         hipError_t e;
+        const int64_t deep = deep_pass_cycles(c, n);
+        if (deep > 0) {
+            Domain &D = c->dom[0];
+            const Dom d = n == deep ? dom_rec(D, c->cur) : dom_for(D, c->cur);
+            e = launch_step_deep(d, D.desc.storage == LBM_FP16_DEV ? ST_F16 : ST_F32, c->deep, (int)deep, c->t == 0,
+                                 c->stream);
+            if (e != hipSuccess) return device_fail(c, e, "step launch");
+            c->cur ^= 1;
+            c->t += deep;
+            n -= deep;
+            if ((e = checkpoint(c)) != hipSuccess) return device_fail(c, e, "checkpoint copy");
+            continue;
+        }
         if (c->t == 0) {
             // collide-only first cycle of every domain
             for (Domain &D : c->dom) {
@@ -1071,6 +1104,7 @@ int lbm_set_schedule(lbm_ctx *c, int32_t tile_w, int32_t vec, int32_t rows, int3
     if (!schedule_supported(s))
         return fail(LBM_EINVAL, "unsupported schedule %d x %d x %d", tile_w, vec, rows);
     c->sched = s;
+    if (c->tblock == 1) c->deep_cycles = 0;   // the caller's shape runs from here on
     reset_graphs(c);
     return LBM_OK;
 }
@@ -1106,6 +1140,7 @@ int lbm_set_time_blocking(lbm_ctx *c, int32_t cycles_per_pass) {
         }
     }
     c->tblock = cycles_per_pass;
+    c->deep_cycles = 0;
     reset_graphs(c);
     return LBM_OK;
 }
@@ -1118,6 +1153,7 @@ int lbm_set_two_cycle_tile(lbm_ctx *c, int32_t threads, int32_t rows) {
     if (c->batch) return fail(LBM_ENOTSUP, "a batch's two-cycle tile is chosen by its autotuner");
     c->tb_threads = threads;
     c->tb_rows = rows;
+    c->deep_cycles = 0;
     reset_graphs(c);
     return LBM_OK;
 }

@@ -14,6 +14,7 @@
 // which the checkpointed recomputation records; never f itself.
 #include <hip/hip_runtime.h>
 
+#include "lbm_deep.h"
 #include "lbm_launch.h"
 
 namespace mrt {

@@ -759,30 +759,22 @@ __device__ __forceinline__ void geq_dev(const Dom &d, float dT, float ux, float 
     out[4] = b - hy;
 }
 
-// Rebuilds the populations f(t) (and g(t)) of a wall node from those of its
-// inner neighbour B at the same time t >= 1 (B's own gather from the
-// post-collision buffer fin):
+// Rebuilds the populations f(t) (and g(t)) of the wall node (x, y) from those of
+// its inner neighbour B at the same time t >= 1, which f and g hold on entry:
 //   f(O) = f^eq(Pi_B, u_w; phi_O) + [f(B) - f^eq(Pi_B, u_B; phi_B)],
 // with Pi = phi p taken over from B, u_B from Eqs. (18)-(19) with B's force,
 // u_w = (U_lid, 0) on the top wall away from on-node x walls and zero
 // elsewhere; g likewise with T_w = Th / Tc on x walls and T_B on y walls.
-template <typename S, bool THERMAL>
-__device__ __forceinline__ void nee_fixup(const Dom &d, const S *__restrict__ fin, int x, int y,
-                                          float f[8], float g[5]) {
-    int bx, by;
-    if (!nee_wall(d, x, y, bx, by)) return;
-    float fB[8], gB[5];
-    gather_general<S>(d, fin, bx, by, fB);
-    const Cell cB = load_cell(d, (int64_t)by * d.pitch + bx);
-    const Cell cO = load_cell(d, (int64_t)y * d.pitch + x);
+template <bool THERMAL>
+__device__ __forceinline__ void nee_rebuild(const Dom &d, int x, int y, const Cell &cB, const Cell &cO, float f[8],
+                                            float g[5]) {
     float ay = d.ay, dTB = 0.0f;
     if (THERMAL) {
-        gather_thermal(d, d.gin, bx, by, false, gB);
-        dTB = (gB[0] + gB[1]) + (gB[2] + gB[3]) + gB[4];
+        dTB = (g[0] + g[1]) + (g[2] + g[3]) + g[4];
         ay = d.ay + d.gbeta * dTB;
     }
     float uxB, uyB, m1B;
-    node_velocity(fB, cB, cB.phi * d.ax, cB.phi * ay, uxB, uyB, m1B);
+    node_velocity(f, cB, cB.phi * d.ax, cB.phi * ay, uxB, uyB, m1B);
     // Eq. (20) on deviations: dPi = (3/5)(dm1 - (2/3)|u|^2/phi)
     const float dPi = mulc(m1B, MRT_C3_5) - mulc((uxB * uxB + uyB * uyB) * cB.inv_phi, MRT_C2_5);
     const bool wx = d.bc_x == BC_NEE && (x == 0 || x == d.nx - 1);
@@ -791,14 +783,78 @@ __device__ __forceinline__ void nee_fixup(const Dom &d, const S *__restrict__ fi
     feq_dev(dPi, uw, 0.0f, cO.inv_phi, eO);
     feq_dev(dPi, uxB, uyB, cB.inv_phi, eB);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) f[i] = eO[i] + (fB[i] - eB[i]);
+    for (int i = 0; i < 8; ++i) f[i] = eO[i] + (f[i] - eB[i]);
     if (THERMAL) {
         const float dTw = wx ? (x == 0 ? d.dTh : d.dTc) : dTB;
         float hO[5], hB[5];
         geq_dev(d, dTw, uw, 0.0f, hO);
         geq_dev(d, dTB, uxB, uyB, hB);
 #pragma unroll
-        for (int j = 0; j < 5; ++j) g[j] = hO[j] + (gB[j] - hB[j]);
+        for (int j = 0; j < 5; ++j) g[j] = hO[j] + (g[j] - hB[j]);
+    }
+}
+
+// The same from HBM: B's own gather from the post-collision buffer fin first.
+template <typename S, bool THERMAL>
+__device__ __forceinline__ void nee_fixup(const Dom &d, const S *__restrict__ fin, int x, int y,
+                                          float f[8], float g[5]) {
+    int bx, by;
+    if (!nee_wall(d, x, y, bx, by)) return;
+    gather_general<S>(d, fin, bx, by, f);
+    if (THERMAL) gather_thermal(d, d.gin, bx, by, false, g);
+    const Cell cB = load_cell(d, (int64_t)by * d.pitch + bx);
+    const Cell cO = load_cell(d, (int64_t)y * d.pitch + x);
+    nee_rebuild<THERMAL>(d, x, y, cB, cO, f, g);
+}
+
+// ---- one node's update, and what a pass writes beside the state ---------
+
+// Thermal-coupled acceleration phi*a of one node (Sec. 3.4 buoyancy on top
+// of the uniform a), and the rest of the per-node update shared by both
+// paths below: collide, then return u.
+template <bool THERMAL>
+__device__ __forceinline__ void node_update(const Dom &d, const Cell &c, float f[8], float g[5],
+                                            float &ux, float &uy, float &n7, float &n8, float &dT) {
+    // half of a (the step works on half forces; every product is halved exactly)
+    float ayh = d.ayh;
+    dT = 0.0f;
+    if (THERMAL) {
+        dT = (g[0] + g[1]) + (g[2] + g[3]) + g[4];
+        ayh = d.ayh + d.gbetah * dT;
+    }
+    collide_h(f, d, c, c.phi * d.axh, c.phi * ayh, ux, uy, n7, n8);
+    if (THERMAL) thermal_collide(g, d, ux, uy);
+}
+
+// Recorded u (and stress moments) of the multi-cycle passes.
+// The records go through buffer stores: a recorded step spans at most five
+// planes, below 4 GiB whenever multi-cycle passes run. They are read back only
+// by the adjoint sweep after the whole segment, so they are streamed past the
+// caches (non-temporal), which keeps the recomputation's own state there
+// (2048^2 recomputation with the adjoint sweep: 6% less time).
+__device__ __forceinline__ void record_node(const Dom &d, BufRes rec, uint32_t o4, float ux, float uy, float n7,
+                                            float n8) {
+    const uint32_t pb4 = (uint32_t)(d.plane * 4);
+    BufIO<float>::st_nt(rec, o4, 0u, ux);
+    BufIO<float>::st_nt(rec, o4, pb4, uy);
+    if (d.rec_stress) {
+        BufIO<float>::st_nt(rec, o4, 2 * pb4, n7);
+        BufIO<float>::st_nt(rec, o4, 3 * pb4, n8);
+    }
+}
+
+// u of a pass's last collision (the velocity one cycle before the state the
+// pass leaves) into the two planes d.uprev, for the steady residual. Only the
+// last pass of an lbm_step call records it; the planes are below 4 GiB
+// whenever multi-cycle passes run.
+__device__ __forceinline__ void store_uprev(const Dom &d, uint32_t o4, float ux, float uy) {
+    const BufRes r = buf_res(d.uprev, (uint32_t)(2 * d.plane * 4));
+    if (d.nt_store) {
+        BufIO<float>::st_nt(r, o4, 0u, ux);
+        BufIO<float>::st_nt(r, o4, (uint32_t)(d.plane * 4), uy);
+    } else {
+        BufIO<float>::st(r, o4, 0u, ux);
+        BufIO<float>::st(r, o4, (uint32_t)(d.plane * 4), uy);
     }
 }
 

@@ -20,23 +20,6 @@ constexpr int BLOCK = 256;
 
 // ------------------------------------------------------------------ step
 
-// Thermal-coupled acceleration phi*a of one node (Sec. 3.4 buoyancy on top
-// of the uniform a), and the rest of the per-node update shared by both
-// paths below: collide, then return u.
-template <bool THERMAL>
-__device__ __forceinline__ void node_update(const Dom &d, const Cell &c, float f[8], float g[5],
-                                            float &ux, float &uy, float &n7, float &n8, float &dT) {
-    // half of a (the step works on half forces; every product is halved exactly)
-    float ayh = d.ayh;
-    dT = 0.0f;
-    if (THERMAL) {
-        dT = (g[0] + g[1]) + (g[2] + g[3]) + g[4];
-        ayh = d.ayh + d.gbetah * dT;
-    }
-    collide_h(f, d, c, c.phi * d.axh, c.phi * ayh, ux, uy, n7, n8);
-    if (THERMAL) thermal_collide(g, d, ux, uy);
-}
-
 // One 256-thread tile: TWT threads along x, each handling NX consecutive
 // nodes in each of ROWS rows (rows TH apart). Tiles that touch no boundary
 // take vector loads of whole rows of NX values per plane; edge tiles gather
@@ -316,23 +299,6 @@ hipError_t launch_step_batch(const Dom *doms, const int4 *tiles, int ntiles, int
                    : launch_batch_t<_Float16, false>(doms, tiles, ntiles, parity, s, grid, st);
 }
 
-// Recorded u (and stress moments) of the multi-cycle passes.
-// The records go through buffer stores: a recorded step spans at most five
-// planes, below 4 GiB whenever multi-cycle passes run. They are read back only
-// by the adjoint sweep after the whole segment, so they are streamed past the
-// caches (non-temporal), which keeps the recomputation's own state there
-// (2048^2 recomputation with the adjoint sweep: 6% less time).
-__device__ __forceinline__ void record_node(const Dom &d, BufRes rec, uint32_t o4, float ux, float uy, float n7,
-                                            float n8) {
-    const uint32_t pb4 = (uint32_t)(d.plane * 4);
-    BufIO<float>::st_nt(rec, o4, 0u, ux);
-    BufIO<float>::st_nt(rec, o4, pb4, uy);
-    if (d.rec_stress) {
-        BufIO<float>::st_nt(rec, o4, 2 * pb4, n7);
-        BufIO<float>::st_nt(rec, o4, 3 * pb4, n8);
-    }
-}
-
 // One node's record held back until the next node's loads have been issued
 // (with THERMAL also dT, plane 4).
 template <bool THERMAL>
@@ -351,21 +317,6 @@ struct Pending {
         on = false;
     }
 };
-
-// u of a pass's last collision (the velocity one cycle before the state the
-// pass leaves) into the two planes d.uprev, for the steady residual. Only the
-// last pass of an lbm_step call records it; the planes are below 4 GiB
-// whenever multi-cycle passes run.
-__device__ __forceinline__ void store_uprev(const Dom &d, uint32_t o4, float ux, float uy) {
-    const BufRes r = buf_res(d.uprev, (uint32_t)(2 * d.plane * 4));
-    if (d.nt_store) {
-        BufIO<float>::st_nt(r, o4, 0u, ux);
-        BufIO<float>::st_nt(r, o4, (uint32_t)(d.plane * 4), uy);
-    } else {
-        BufIO<float>::st(r, o4, 0u, ux);
-        BufIO<float>::st(r, o4, (uint32_t)(d.plane * 4), uy);
-    }
-}
 
 // ------------------------------------------------- two steps per pass
 

@@ -84,6 +84,16 @@ hipError_t launch_step2_batch(const Dom *doms, const int4 *tiles, int ntiles, in
                               bool thermal, bool uniform, int threads, int rows, int grid, hipStream_t st);
 const void *step2_batch_kernel_fn(int storage, bool thermal, bool uniform, bool one, int threads, int rows);
 
+// The deep pass (lbm_deep.h): C cycles in one launch on tiles_x x tiles_y tiles
+// of nearly equal size. direct: the state is f(0) itself (t = 0).
+struct DeepPlan {
+    int tiles_x, tiles_y;
+};
+// The plan of a domain that the deep pass serves and the most cycles per launch
+// (false: another pass is faster).
+bool deep_plan(const Dom &d, DeepPlan *plan, int *cycles);
+hipError_t launch_step_deep(const Dom &d, int storage, const DeepPlan &p, int cycles, bool direct, hipStream_t st);
+
 // Persistent batched step over a tile table: doms[2*k + parity] describes
 // domain k with its buffers for this parity; tiles[j] = (domain, tx, ty, 0).
 // thermal: every domain of the table carries the D2Q5 field (or none does).
