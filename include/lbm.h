@@ -330,9 +330,11 @@ int lbm_set_time_blocking(lbm_ctx *c, int32_t cycles_per_pass);
 /* Small single domains (up to about 300,000 nodes isothermal, 200,000 with
  * the thermal model, about a million with on-node walls) step by deep passes
  * of up to ten cycles per launch, and domains of a few hundred nodes by up to
- * 1024, until the caller sets a mode here, a tile (lbm_set_two_cycle_tile) or,
- * with on-node walls, a launch shape (lbm_set_schedule); the mode reported
- * below is then the one that fills in. Same bits as every other pass. */
+ * 1024; large ones (isothermal, no 1/K or viscosity plane, from 2^22 nodes)
+ * by strip passes of six and four cycles. The mode reported below fills in
+ * where they do not fit. A mode set here (and for the small ones a tile set by
+ * lbm_set_two_cycle_tile or, with on-node walls, a launch shape) replaces
+ * them. Same bits as every other pass. */
 
 /* Current cycles per pass, and the workgroup size, tile rows (tiles are 64
  * nodes wide) and grid size of the multi-cycle pass it runs: the four-cycle
@@ -353,7 +355,7 @@ int lbm_set_two_cycle_tile(lbm_ctx *c, int32_t threads, int32_t rows);
 
 /* Number of steps lbm_step replays from one hand-built HIP graph of kernel
  * nodes (up to 4096, rounded down to a whole number of passes; 0 launches
- * every step separately). Deep passes are launched directly.
+ * every step separately). Deep and strip passes are launched directly.
  * Defaults: 0 for single domains, 32 for batches. Graphs are not used while
  * a trajectory is recorded for lbm_backward. Results do not depend on it. */
 int lbm_set_graph_steps(lbm_ctx *c, int32_t steps);

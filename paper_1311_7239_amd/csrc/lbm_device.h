@@ -564,7 +564,13 @@ template <> struct MediumSrc<MK_BRANCHED> {
 template <> struct MediumSrc<MK_UNIFORM> {
     __device__ explicit MediumSrc(const Dom &) {}
     __device__ CellRaw load(uint32_t) const { return CellRaw{0.0f, 0.0f, 0.0f}; }
-    __device__ Cell cell(const Dom &d, const CellRaw &) const { return cell_from(d, 0.0f, 0.0f); }
+    __device__ Cell cell(const Dom &d, const CellRaw &) const {   // cell_from's uniform branch, without the test
+        Cell c;
+        c.s_nu = d.s_nu; c.h_nu = d.h_nu; c.h_nu2 = d.h_nu2; c.h_nu4 = d.h_nu4;
+        c.phi = d.phi0; c.inv_phi = d.inv_phi0; c.cd = d.cd0; c.cf = d.cf0;
+        c.cdh = d.cd0h; c.cfh = d.cf0h;
+        return c;
+    }
 };
 template <> struct MediumSrc<MK_ERGUN> {
     BufRes phi;

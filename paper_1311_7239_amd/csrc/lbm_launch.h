@@ -94,6 +94,15 @@ struct DeepPlan {
 bool deep_plan(const Dom &d, DeepPlan *plan, int *cycles);
 hipError_t launch_step_deep(const Dom &d, int storage, const DeepPlan &p, int cycles, bool direct, hipStream_t st);
 
+// The strip pass (lbm_strip.h): the domain in `strips` column strips and `chunks`
+// runs of rows, one wavefront each.
+struct StripPlan {
+    int strips, chunks;
+};
+bool strip_domain(const Dom &d, int storage);   // whether the pass serves a domain
+int strip_cycles(int64_t n);                     // cycles of the next pass with n left
+hipError_t launch_step_strip(const Dom &d, int storage, int cycles, hipStream_t st);   // cycles: 4 or 6
+
 // Persistent batched step over a tile table: doms[2*k + parity] describes
 // domain k with its buffers for this parity; tiles[j] = (domain, tx, ty, 0).
 // thermal: every domain of the table carries the D2Q5 field (or none does).

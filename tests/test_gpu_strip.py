@@ -1,0 +1,77 @@
+"""The strip pass (six and four cycles per launch on large domains, the default there)
+against the one-cycle pass, bit for bit: periodic and walled axes, odd widths (a lane's two
+columns across a seam, half a pair at the end), both storages, uniform and Ergun media,
+calls of every remainder, the residual's u(t - 1) planes and a recorded pass. Equal inputs
+and the same per-node arithmetic, so the tolerance is zero."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1311_7239_amd import inputs as I
+from paper_1311_7239_amd import lbm
+
+pytestmark = pytest.mark.gpu
+
+
+def _phi(nx, ny):
+    x, y = np.arange(nx, dtype=np.float32), np.arange(ny, dtype=np.float32)
+    g = np.outer(np.sin(0.05 * y), np.cos(0.03 * x)) + np.outer(np.cos(0.011 * y), np.sin(0.2 * x))
+    return np.clip(0.45 + 0.15 * g, 0.1, 0.95).astype(np.float32)
+
+
+def _case(bc_x, bc_y, nx, ny, ergun):
+    c = I.lid_cavity(n=64)
+    c.nx, c.ny, c.bc_x, c.bc_y, c.nu, c.ax, c.ay = nx, ny, bc_x, bc_y, 0.1, 1e-6, -2e-6
+    c.lid_ux = 0.05 if bc_y == I.WALLS else 0.0
+    if ergun:
+        c.phi, c.dp, c.Fphi = _phi(nx, ny), I.ergun_dp(30.0, 0.4), None
+    return c
+
+
+P, W = I.PERIODIC, I.WALLS
+CASES = [
+    (P, W, 2048, 2049, True, lbm.FP32_DEV),
+    (P, W, 4099, 1025, True, lbm.FP32_DEV),     # odd periodic width
+    (P, P, 1161, 3700, True, lbm.FP32_DEV),     # its last strip is a column wide before it takes its ring
+    (W, W, 2047, 2052, True, lbm.FP32_DEV),
+    (W, P, 16385, 257, True, lbm.FP32_DEV),     # ends in half a pair
+    (W, W, 2931, 2901, False, lbm.FP32_DEV),
+    (P, W, 3001, 2101, True, lbm.FP16_DEV),     # odd pairs in binary16
+    (P, W, 2900, 2935, False, lbm.FP16_DEV),
+    (W, P, 2600, 2431, False, lbm.FP16_DEV),
+]
+
+
+@pytest.mark.parametrize("bc_x,bc_y,nx,ny,ergun,storage", CASES)
+def test_strip_pass_is_bitwise_the_one_cycle_pass(bc_x, bc_y, nx, ny, ergun, storage):
+    case = _case(bc_x, bc_y, nx, ny, ergun)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(nx)
+    df = 2e-3 * (torch.rand((8, ny, nx), generator=g, device="cuda") - 0.5)
+    a, b = (lbm.solver_for_case(case, storage=storage) for _ in range(2))
+    a.set_time_blocking(1)
+    for s in (a, b):
+        s.set_populations(df)
+    for chunk in (7, 4, 6, 11, 13):     # the collide-only cycle and 6; 4; 6; 4 + 4 + 3; 6 + 4 + 3
+        a.step(chunk)
+        b.step(chunk)
+        fa, fb = a.populations()[0], b.populations()[0]
+        torch.cuda.synchronize()
+        assert torch.equal(fa, fb), (chunk, a.time)
+        assert a.reduce() == b.reduce(), (chunk, a.time)
+
+
+def test_strip_passes_stop_at_checkpoints():
+    """The gradient recomputes from the checkpoints, so equal gradients need equal checkpoints."""
+    case = _case(P, W, 2100, 2001, True)
+    out = []
+    for cycles in (1, 0):
+        s = lbm.solver_for_case(case, ckpt_every=9, max_steps_recorded=24)
+        if cycles:
+            s.set_time_blocking(cycles)
+        s.step(24)
+        _, u, _ = s.macroscopic()
+        g, _ = s.backward(u)
+        torch.cuda.synchronize()
+        out.append((u, g))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
