@@ -445,17 +445,27 @@ hipError_t checkpoint(lbm_ctx *c) {
 
 namespace {
 
-// Cycles of the next deep pass of a call with n cycles left (0: another pass):
-// passes of equal length, none over a checkpoint. Below three cycles the launch
-// and the ring of a larger domain cost more than the other passes (450^2 cavity,
-// one step per call: 20 us against 16; 20 x 500: 15 and 15).
-int64_t deep_pass_cycles(const lbm_ctx *c, int64_t n) {
-    if (c->deep_cycles <= 0) return 0;
-    const lbm_desc &d = c->dom[0].desc;
-    if (c->rec_valid && d.ckpt_every > 0) n = std::min<int64_t>(n, d.ckpt_every - c->t % d.ckpt_every);
-    if (n < 3 && (int64_t)d.nx * d.ny > 65536) return 0;
-    const int64_t passes = (n + c->deep_cycles - 1) / c->deep_cycles;
+// Cycles of the next of several deep passes over n cycles, `most` at a time (0:
+// none): passes of equal length.
+int64_t deep_cycles_of(int most, int64_t n) {
+    if (most <= 0) return 0;
+    const int64_t passes = (n + most - 1) / most;
     return (n + passes - 1) / passes;
+}
+
+// The same for the next n cycles of a run (0: another pass). Below three cycles
+// the launch and the ring of a larger domain cost more than the other passes (450^2
+// cavity, one step per call: 20 us against 16; 20 x 500: 15 and 15).
+int64_t deep_run_cycles(const lbm_ctx *c, int64_t n) {
+    const lbm_desc &d = c->dom[0].desc;
+    return n < 3 && (int64_t)d.nx * d.ny > 65536 ? 0 : deep_cycles_of(c->deep_cycles, n);
+}
+
+// And of an lbm_step call with n cycles left: none over a checkpoint.
+int64_t deep_pass_cycles(const lbm_ctx *c, int64_t n) {
+    const int every = c->dom[0].desc.ckpt_every;
+    if (c->rec_valid && every > 0) n = std::min<int64_t>(n, every - c->t % every);
+    return deep_run_cycles(c, n);
 }
 
 // cycles advanced by one kernel node of the step graph
@@ -1632,6 +1642,10 @@ int backward_impl(lbm_ctx *c, const float *dL_du, float *dL_dphi, float *dL_dkap
     double *acc_step = acc ? acc + 4 * adjoint_theta_offset(d.nx, d.ny, 1) : nullptr;
     double *acc_step2 = acc ? acc + 4 * adjoint_theta_offset(d.nx, d.ny, 2) : nullptr;
     hipStream_t st = c->stream;
+    // small domains: deep passes both ways (the same bits again)
+    DeepPlan adeep{};
+    int adeep_cycles = 0;
+    if (c->deep_cycles > 0 && !adjoint_deep_plan(D.dom, (int64_t)L.theta_slots, &adeep, &adeep_cycles)) adeep_cycles = 0;
 
     hipError_t e = hipSuccess;
     if (acc) e = launch_fill_zero(acc, sizeof(double) * 4 * (L.theta_slots + 1), st);
@@ -1660,7 +1674,10 @@ int backward_impl(lbm_ctx *c, const float *dL_du, float *dL_dphi, float *dL_dkap
                     dr.gin = (const float *)(D.base + L.off_rg[p]);
                     dr.gout = (float *)(D.base + L.off_rg[p ^ 1]);
                 }
-                if (rec4 && t > 0 && t + 3 < s1) {
+                if (const int64_t deep = deep_run_cycles(c, s1 - t); deep > 0) {
+                    e = launch_step_deep_rec(dr, c->deep, (int)deep, t == 0, st);
+                    t += deep;
+                } else if (rec4 && t > 0 && t + 3 < s1) {
                     // four cycles in one pass, recording at t, t + 1, t + 2 and t + 3
                     e = launch_step4_rec(dr, c->sched.swizzle, dr.urec + rstride, dr.urec + 2 * rstride,
                                          dr.urec + 3 * rstride, st);
@@ -1683,7 +1700,11 @@ int backward_impl(lbm_ctx *c, const float *dL_du, float *dL_dphi, float *dL_dkap
             // backward through the segment (two or three steps per pass in the multi-cycle modes)
             for (int64_t t = s1 - 1; t >= s0;) {
                 const float *ut = urec + (size_t)(t - s0) * rstride;
-                if (th && c->tblock >= 2 && t - 1 >= s0) {
+                if (const int64_t deep = deep_cycles_of(adeep_cycles, t + 1 - s0); deep > 0) {
+                    e = launch_adjoint_deep(D.dom, adeep, (int)deep, lam[la], lam[la ^ 1], lamg[la], lamg[la ^ 1], ut,
+                                            gphi, gk, acc, st);
+                    t -= deep;
+                } else if (th && c->tblock >= 2 && t - 1 >= s0) {
                     e = launch_adjoint_step2_thermal(D.dom, lam[la], lam[la ^ 1], lamg[la], lamg[la ^ 1], ut,
                                                      ut - rstride, gphi, gk, acc_step2, st);
                     t -= 2;

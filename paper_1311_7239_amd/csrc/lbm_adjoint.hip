@@ -31,9 +31,11 @@ struct ParamBar {
 
 // Per-thread sums of the adjoints of the scalar parameters: nu, a_x, a_y and
 // the lid velocity.
-struct ThetaSum {
-    float nu, ax, ay, lid;
+template <typename R>
+struct ThetaSumOf {
+    R nu, ax, ay, lid;
 };
+typedef ThetaSumOf<float> ThetaSum;
 
 // A node's share of dL/dnu, dL/da_x, dL/da_y at one step: a enters as phi a;
 // nu enters the linear drag cd = phi nu / K (Eq. 3) and s_nu = 1/(1/2 + 3 J nu)
@@ -52,8 +54,8 @@ __device__ __forceinline__ float lid_share(const Dom &d, int y, float a6, float 
 
 // Adds the block's sums of ts to slot[0..3] in a fixed order (bitwise
 // reproducible); every thread of the block calls it.
-template <int NT>
-__device__ __forceinline__ void block_theta_add(const ThetaSum &ts, double *slot) {
+template <int NT, typename R>
+__device__ __forceinline__ void block_theta_add(const ThetaSumOf<R> &ts, double *slot) {
     __shared__ double red[NT / 64][4];
     double v[4] = {ts.nu, ts.ax, ts.ay, ts.lid};
 #pragma unroll
@@ -212,22 +214,41 @@ __device__ __forceinline__ void cell_phi_derivs(const Dom &d, const Cell &c, flo
     }
 }
 
+// What a node's medium gradient multiplies the adjoints of cd and cf by: d cd, d cf
+// by d phi, and d cf by d kappa.
+struct MediumDerivs {
+    float dcd, dcf, dcf_dk;
+};
+
+template <int MK = MK_ANY>
+__device__ __forceinline__ MediumDerivs medium_derivs(const Dom &d, const Cell &c, float kappa) {
+    MediumDerivs m;
+    cell_phi_derivs<MK>(d, c, kappa, m.dcd, m.dcf);
+    m.dcf_dk = 0.0f;
+    if (MK == MK_ANY && d.medium == MED_PHI_KAPPA) {
+        const float F = (d.Fconst >= 0.0f) ? d.Fconst : ergun_F(c.inv_phi);
+        const float sq = hw_sqrt(kappa);
+        m.dcf_dk = (kappa > 0.0f) ? 0.5f * c.phi * F * hw_rcp(sq) : 0.0f;
+    }
+    return m;
+}
+
 // Medium adjoints -> dL/dphi (and dL/dkappa with a kappa plane).
+template <int MK = MK_ANY>
+__device__ __forceinline__ void medium_gradient(const Dom &d, const Cell &c, const MediumDerivs &m,
+                                                const ParamBar &pb, float ax, float ay,
+                                                float &gphi, float &gkappa) {
+    const float ip = c.inv_phi;
+    gkappa = 0.0f;
+    if (MK == MK_ANY && d.medium == MED_PHI_KAPPA) gkappa = pb.cd * c.phi * d.nu + pb.cf * m.dcf_dk;
+    gphi = ax * pb.pax + ay * pb.pay + pb.cd * m.dcd + pb.cf * m.dcf - pb.ip * ip * ip;
+}
+
 template <int MK = MK_ANY>
 __device__ __forceinline__ void medium_gradient(const Dom &d, const Cell &c, float kappa,
                                                 const ParamBar &pb, float ax, float ay,
                                                 float &gphi, float &gkappa) {
-    const float phi = c.phi, ip = c.inv_phi;
-    float dcd, dcf;
-    cell_phi_derivs<MK>(d, c, kappa, dcd, dcf);
-    gkappa = 0.0f;
-    if (MK == MK_ANY && d.medium == MED_PHI_KAPPA) {
-        const float F = (d.Fconst >= 0.0f) ? d.Fconst : ergun_F(ip);
-        const float sq = hw_sqrt(kappa);
-        const float dcf_dk = (kappa > 0.0f) ? 0.5f * phi * F * hw_rcp(sq) : 0.0f;
-        gkappa = pb.cd * phi * d.nu + pb.cf * dcf_dk;
-    }
-    gphi = ax * pb.pax + ay * pb.pay + pb.cd * dcd + pb.cf * dcf - pb.ip * ip * ip;
+    medium_gradient<MK>(d, c, medium_derivs<MK>(d, c, kappa), pb, ax, ay, gphi, gkappa);
 }
 
 __device__ __forceinline__ float kappa_at(const Dom &d, int64_t o) {
@@ -1109,6 +1130,213 @@ hipError_t launch_adjoint_step_thermal(const Dom &d, const float *lam_in, float 
     else
         hipLaunchKernelGGL(k_adjoint_step_thermal<false>, grid, dim3(ABLOCK), 0, st, d, lam_in, lam_out, lamg_in,
                            lamg_out, u_t, gphi, gkappa, tiles_x, acc);
+    return hipGetLastError();
+}
+
+// The reverse mode of the deep pass: C backward steps per launch for domains that
+// leave most of the chip idle, on the same tiles and rings (the transposed gather
+// pulls from x + e instead of x - e, so it is the same frame with the directions
+// turned round). One node per thread: its LDS sources, its cell, the derivatives
+// of its drag and its running medium gradient stay in registers for the whole
+// pass, the next step's record is loaded before this step's collision. The
+// gradient adds one step after the other, so the result is bitwise that of single
+// steps; the parameter sums, which run over many steps here, are in FP64.
+//
+// What bounds it: a launch, the load and the store of the frame (about 5 us per
+// launch), and the issue of one wavefront of nodes per 64 threads in each step. A
+// whole backward pass, with its recomputation (segments of 50 steps, us per step):
+// 320^2 with the thermal model and parameter gradients 11.1 -> 6.3, of which 4.0
+// here (7.2 in two-step tiles); 160^2 isothermal 7.6 -> 2.6, 400^2 8.2 -> 5.6.
+template <bool THETA, bool THERMAL, int NT>
+__global__ __launch_bounds__(NT) void k_adjoint_deep(Dom d, DeepPlan p, int C, const float *__restrict__ lam_in,
+                                                     float *__restrict__ lam_out, const float *__restrict__ lamg_in,
+                                                     float *__restrict__ lamg_out, const float *__restrict__ u_t,
+                                                     float *__restrict__ gphi, float *__restrict__ gkappa,
+                                                     double *__restrict__ acc) {
+    constexpr int CAP = NT;
+    __shared__ float lds[2 * 8 * CAP];
+    __shared__ float ldsg[THERMAL ? 2 * 5 * CAP : 1];
+    const DeepFrame F(d, p, C);
+    const uint32_t pb4 = (uint32_t)(d.plane * 4);
+    const BufRes rg = buf_res(gphi, pb4), rgk = buf_res(gkappa, gkappa ? pb4 : 0u);
+    const MediumSrc<MK_ANY> med(d);
+    const int s = (int)threadIdx.x;
+    ThetaSumOf<double> ts{0.0, 0.0, 0.0, 0.0};   // over many steps
+
+    if (s < F.n) {
+        const BufRes rl = buf_res(lam_in, 8 * pb4), rlg = buf_res(THERMAL ? lamg_in : nullptr, THERMAL ? 5 * pb4 : 0u);
+        int at;
+        const uint32_t v = F.offset(s, 1.0f / (float)F.w, d.pitch, at) * 4;
+        float a[8], ag[5];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a[i] = BufIO<float>::ld(rl, v, (uint32_t)i * pb4);
+        if (THERMAL) {
+#pragma unroll
+            for (int j = 0; j < 5; ++j) ag[j] = BufIO<float>::ld(rlg, v, (uint32_t)j * pb4);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) lds[i * CAP + at] = a[i];
+        if (THERMAL) {
+#pragma unroll
+            for (int j = 0; j < 5; ++j) ldsg[j * CAP + at] = ag[j];
+        }
+    }
+
+    int x, y, src[8], gsrc[5], own = 0;
+    int ring = deep_node(F.X, F.Y, C, s, x, y);
+    uint32_t o4 = 0, minus = 0;   // minus: D2Q5 links that come back from an isothermal wall
+    bool top = false;
+    Cell c;
+    MediumDerivs md{0.0f, 0.0f, 0.0f};
+    float gp = 0.0f, gk = 0.0f;
+    struct Rec {
+        float ux, uy, n7, n8, dT;
+    };
+    auto record = [&](int k) -> Rec {
+        const BufRes r = buf_res(u_t - (int64_t)k * 5 * d.plane, 5 * pb4);
+        return Rec{BufIO<float>::ld(r, o4, 0u), BufIO<float>::ld(r, o4, pb4),
+                   THETA ? BufIO<float>::ld(r, o4, 2 * pb4) : 0.0f, THETA ? BufIO<float>::ld(r, o4, 3 * pb4) : 0.0f,
+                   THERMAL ? BufIO<float>::ld(r, o4, 4 * pb4) : 0.0f};
+    };
+    Rec next{0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    if (ring >= C || x >= F.X.last(C) || y >= F.Y.last(C)) {
+        ring = C;   // no node left for this thread
+    } else {
+        const int gx = F.wrapped(x, d.nx), gy = F.wrapped(y, d.ny);
+        o4 = (uint32_t)(gy * d.pitch + gx) * 4;
+        own = (y - F.y0) * F.s + (x - F.x0);
+        next = record(0);
+        const CellRaw raw = med.load(o4);
+        c = med.cell(d, raw);
+        if (ring == 0) {
+            md = medium_derivs(d, c, raw.kappa);
+            gp = BufIO<float>::ld(rg, o4, 0u);
+            gk = gkappa ? BufIO<float>::ld(rgk, o4, 0u) : 0.0f;
+        }
+        const DeepLinks at(F, gx, gy, x - F.x0, y - F.y0);
+        top = d.bc_y == BC_WALLS && gy == d.ny - 1;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) src[i] = at.source(-EX[i], -EY[i], i, OPP[i], CAP);
+        if (THERMAL) {
+#pragma unroll
+            for (int j = 0; j < 5; ++j) gsrc[j] = at.source(-TXv[j], -TYv[j], j, TOPP[j], CAP);
+            minus = (at.outr ? 1u << 1 : 0u) | (at.outl ? 1u << 3 : 0u);
+        }
+    }
+
+    auto step = [&](int k, const float *from, const float *fromg, float *to, float *tog) {
+        lds_barrier();
+        if (ring > C - 1 - k) return;
+        const Rec u = next;
+        if (k + 1 < C) next = record(k + 1);
+        float b[8], bg[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f}, a[8], ag[5], ubx = 0.0f, uby = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b[i] = from[src[i]];
+        if (THERMAL) {
+#pragma unroll
+            for (int j = 0; j < 5; ++j) {
+                const float v = fromg[gsrc[j]];
+                bg[j] = (minus >> j) & 1u ? -v : v;
+            }
+            thermal_collide_adjoint(bg, d, u.ux, u.uy, u.dT, ag, ubx, uby);
+        }
+        const float ay = THERMAL ? d.ay + d.gbeta * u.dT : d.ay;
+        ParamBar pb;
+        collide_adjoint(b, d, c, c.phi * d.ax, c.phi * ay, u.ux, u.uy, u.n7, u.n8, a, pb, ubx, uby);
+        const float Tb = THERMAL ? c.phi * d.gbeta * pb.pay : 0.0f;
+        if (ring == 0) {
+            float p1, k1;
+            medium_gradient(d, c, md, pb, d.ax, ay, p1, k1);
+            gp += p1;
+            if (gkappa) gk += k1;
+            if (THETA) {
+                ThetaSum one{0.0f, 0.0f, 0.0f, 0.0f};
+                theta_add(d, c, pb, one);
+                if (top) one.lid = lid_share(d, d.ny - 1, from[6 * CAP + own], from[7 * CAP + own]);
+                ts.nu += one.nu;
+                ts.ax += one.ax;
+                ts.ay += one.ay;
+                ts.lid += one.lid;
+            }
+        }
+        if (k < C - 1) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) to[i * CAP + own] = a[i];
+            if (THERMAL) {
+#pragma unroll
+                for (int j = 0; j < 5; ++j) tog[j * CAP + own] = ag[j] + Tb;
+            }
+            return;
+        }
+        const BufRes rl = buf_res(lam_out, 8 * pb4), rlg = buf_res(THERMAL ? lamg_out : nullptr, THERMAL ? 5 * pb4 : 0u);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) BufIO<float>::st(rl, o4, (uint32_t)i * pb4, a[i]);
+        if (THERMAL) {
+#pragma unroll
+            for (int j = 0; j < 5; ++j) BufIO<float>::st(rlg, o4, (uint32_t)j * pb4, ag[j] + Tb);
+        }
+        BufIO<float>::st(rg, o4, 0u, gp);
+        if (gkappa) BufIO<float>::st(rgk, o4, 0u, gk);
+    };
+    float *ldsB = lds + 8 * CAP, *ldsgB = ldsg + (THERMAL ? 5 * CAP : 0);
+    for (int k = 0; k < C; k += 2) {
+        step(k, lds, ldsg, ldsB, ldsgB);
+        if (k + 1 < C) step(k + 1, ldsB, ldsgB, lds, ldsg);
+    }
+    if (THETA) block_theta_add<NT>(ts, acc + 4 * (int64_t)blockIdx.x);
+}
+
+// Where it is taken and its tiles: as the forward pass (one workgroup for the
+// whole domain where that pass uses one, else a tile per CU), but frames of one node
+// per thread only, and the most steps up to ten that those hold, from three on (320^2
+// with heat, 400 nodes a tile: four steps 6.7, five 6.3; 160^2: five 4.5, eight
+// 4.3, ten 4.1). A parameter gradient needs a slot per tile: narrow or flat
+// domains with fewer take fewer tiles.
+constexpr int ADJ_DEEP_CAP = 1024, ADJ_DEEP_MOST = 10, ADJ_DEEP_LEAST = 3;
+
+bool adjoint_deep_plan(const Dom &d, int64_t slots, DeepPlan *plan, int *cycles) {
+    const int64_t nodes = (int64_t)d.nx * d.ny;
+    if (nodes <= (d.thermal ? 640 : 800)) {
+        *plan = DeepPlan{1, 1, 0};
+        *cycles = 1024;
+        return slots >= 1;
+    }
+    const int wgs = (int)std::min<int64_t>(256, slots);
+    if (wgs < 1) return false;
+    int tx = (int)(std::sqrt((double)wgs * d.nx / d.ny) + 0.5);
+    tx = std::min(std::max(tx, 1), std::min(d.nx, wgs));
+    const DeepPlan p{tx, std::min(wgs / tx, d.ny), 0};
+    for (int C = ADJ_DEEP_MOST; C >= ADJ_DEEP_LEAST; --C) {
+        const int n = deep_fits(d, p, C) ? deep_frame(d, p, C) : 0;
+        if (n == 0 || n > ADJ_DEEP_CAP) continue;
+        *plan = p;
+        *cycles = C;
+        return true;
+    }
+    return false;
+}
+
+hipError_t launch_adjoint_deep(const Dom &d, const DeepPlan &p, int C, const float *lam_in, float *lam_out,
+                               const float *lamg_in, float *lamg_out, const float *u_t, float *gphi, float *gkappa,
+                               double *acc, hipStream_t st) {
+    const int n = deep_fits(d, p, C) ? deep_frame(d, p, C) : 0;
+    if (n == 0 || n > ADJ_DEEP_CAP || d.bc_x == BC_NEE || d.bc_y == BC_NEE) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(p.tiles_x * p.tiles_y));
+    const DeepPlan q{p.tiles_x, p.tiles_y, deep_stride(d, p, C)};
+#define MRT_ADJD(TH, THERMAL, NT) \
+    hipLaunchKernelGGL((k_adjoint_deep<TH, THERMAL, NT>), grid, dim3(NT), 0, st, d, q, C, lam_in, lam_out, lamg_in, \
+                       lamg_out, u_t, gphi, gkappa, acc)
+#define MRT_ADJD_N(TH, THERMAL) \
+    do { \
+        if (n <= 512) MRT_ADJD(TH, THERMAL, 512); \
+        else MRT_ADJD(TH, THERMAL, 1024); \
+    } while (0)
+    if (d.thermal && acc) MRT_ADJD_N(true, true);
+    else if (d.thermal) MRT_ADJD_N(false, true);
+    else if (acc) MRT_ADJD_N(true, false);
+    else MRT_ADJD_N(false, false);
+#undef MRT_ADJD_N
+#undef MRT_ADJD
     return hipGetLastError();
 }
 

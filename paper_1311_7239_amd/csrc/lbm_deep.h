@@ -81,35 +81,90 @@ __device__ __forceinline__ int deep_node(const DeepAxis &X, const DeepAxis &Y, i
     return g;
 }
 
-template <typename S, int MK, bool THERMAL, bool NEE, int CAP, int NT>
+// A workgroup's tile with its ring as it lies in LDS: the nodes that cycle 0
+// reads, row by row.
+struct DeepFrame {
+    DeepAxis X, Y;
+    int x0, y0, w, n, s;   // s: row stride in LDS
+    bool per_x, per_y, wrap_x, wrap_y;   // wrap: a periodic axis that one tile covers
+    int nx, ny;
+    __device__ DeepFrame(const Dom &d, const DeepPlan &p, int C)
+        : X((int)blockIdx.x % p.tiles_x, p.tiles_x, d.nx, d.bc_x == BC_PERIODIC),
+          Y((int)blockIdx.x / p.tiles_x, p.tiles_y, d.ny, d.bc_y == BC_PERIODIC) {
+        x0 = X.first(C);
+        y0 = Y.first(C);
+        w = X.last(C) - x0;
+        n = w * (Y.last(C) - y0);
+        s = p.stride;
+        per_x = d.bc_x == BC_PERIODIC;
+        per_y = d.bc_y == BC_PERIODIC;
+        wrap_x = p.tiles_x == 1 && per_x;
+        wrap_y = p.tiles_y == 1 && per_y;
+        nx = d.nx;
+        ny = d.ny;
+    }
+    __device__ static int wrapped(int v, int m) { return v < 0 ? v + m : (v >= m ? v - m : v); }
+    // node offset in a plane, and LDS position, of the frame's k-th node
+    __device__ uint32_t offset(int k, float inv, int pitch, int &at) const {
+        const int row = small_div(k, inv), col = k - row * w;
+        at = row * s + col;
+        return (uint32_t)(wrapped(y0 + row, ny) * pitch + wrapped(x0 + col, nx));
+    }
+};
+
+// LDS columns and row offsets of a node (bx, by), at column cx and row cy of the
+// frame, and of the nodes beside it, and the walls next to it.
+struct DeepLinks {
+    int cx, colm, colp, row0, rowm, rowp;
+    bool outl, outr, outb, outt;
+    __device__ DeepLinks(const DeepFrame &F, int bx, int by, int cx_, int cy) {
+        const bool xl = bx == 0, xr = bx == F.nx - 1, yl = by == 0, yr = by == F.ny - 1;
+        cx = cx_;
+        colm = xl && F.wrap_x ? F.nx - 1 : cx - 1;
+        colp = xr && F.wrap_x ? 0 : cx + 1;
+        row0 = cy * F.s;
+        rowm = (yl && F.wrap_y ? F.ny - 1 : cy - 1) * F.s;
+        rowp = (yr && F.wrap_y ? 0 : cy + 1) * F.s;
+        outl = xl && !F.per_x;
+        outr = xr && !F.per_x;
+        outb = yl && !F.per_y;
+        outt = yr && !F.per_y;
+    }
+    // position (planes of `cap` floats) of what comes along (ex, ey): plane `plane`
+    // of the node at -(ex, ey), or across a wall the own plane `oplane`
+    __device__ int source(int ex, int ey, int plane, int oplane, int cap) const {
+        const bool out = (ex > 0 && outl) || (ex < 0 && outr) || (ey > 0 && outb) || (ey < 0 && outt);
+        const int at = (ey > 0 ? rowm : (ey < 0 ? rowp : row0)) + (ex > 0 ? colm : (ex < 0 ? colp : cx));
+        return out ? oplane * cap + row0 + cx : plane * cap + at;
+    }
+};
+
+// REC: every cycle also records its velocity for the adjoint (and the stress
+// moments and the temperature), cycle k five planes after cycle k - 1.
+template <typename S, int MK, bool THERMAL, bool NEE, bool REC, int CAP, int NT>
 __global__ __launch_bounds__(NT) void k_step_deep(Dom d, DeepPlan p, int C, int direct) {
     constexpr int R = (CAP + NT - 1) / NT;
     constexpr int ES = (int)sizeof(S);
     __shared__ float lds[2 * 8 * CAP];
     __shared__ float ldsg[THERMAL ? 2 * 5 * CAP : 1];
-    const bool per_x = d.bc_x == BC_PERIODIC, per_y = d.bc_y == BC_PERIODIC;
-    const DeepAxis X((int)blockIdx.x % p.tiles_x, p.tiles_x, d.nx, per_x);
-    const DeepAxis Y((int)blockIdx.x / p.tiles_x, p.tiles_y, d.ny, per_y);
-    // the frame: what cycle 0 reads
-    const int fx0 = X.first(C), fy0 = Y.first(C), fw = X.last(C) - fx0, fn = fw * (Y.last(C) - fy0);
+    const DeepFrame F(d, p, C);
     const uint32_t fbytes = (uint32_t)(8 * d.plane * ES);
     const BufRes rin = buf_res(d.fin, fbytes), rout = buf_res(d.fout, fbytes);
     const uint32_t gbytes = THERMAL ? (uint32_t)(5 * d.plane * 4) : 0u;
     const BufRes rgin = buf_res(THERMAL ? d.gin : nullptr, gbytes), rgout = buf_res(THERMAL ? d.gout : nullptr, gbytes);
     const MediumSrc<MK> med(d);
-    auto wrapped = [&](int v, int n) -> int { return v < 0 ? v + n : (v >= n ? v - n : v); };
 
     // the frame's populations into the first LDS buffer, row by row
     float *ldsB = lds + 8 * CAP, *ldsgB = ldsg + (THERMAL ? 5 * CAP : 0);
     {
-        const float inv = 1.0f / (float)fw;
+        const float inv = 1.0f / (float)F.w;
         float f[R][8], g[R][THERMAL ? 5 : 1];
+        int at[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int s = (int)threadIdx.x + r * NT;
-            if (s >= fn) continue;
-            const int row = small_div(s, inv);
-            const uint32_t v = (uint32_t)(wrapped(fy0 + row, d.ny) * d.pitch + wrapped(fx0 + s - row * fw, d.nx));
+            if (s >= F.n) continue;
+            const uint32_t v = F.offset(s, inv, d.pitch, at[r]);
 #pragma unroll
             for (int i = 0; i < 8; ++i) f[r][i] = BufIO<S>::ld(rin, v * ES, (uint32_t)(i * d.plane * ES));
             if (THERMAL) {
@@ -120,12 +175,12 @@ __global__ __launch_bounds__(NT) void k_step_deep(Dom d, DeepPlan p, int C, int 
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int s = (int)threadIdx.x + r * NT;
-            if (s >= fn) continue;
+            if (s >= F.n) continue;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) lds[i * CAP + s] = f[r][i];
+            for (int i = 0; i < 8; ++i) lds[i * CAP + at[r]] = f[r][i];
             if (THERMAL) {
 #pragma unroll
-                for (int j = 0; j < 5; ++j) ldsg[j * CAP + s] = g[r][THERMAL ? j : 0];
+                for (int j = 0; j < 5; ++j) ldsg[j * CAP + at[r]] = g[r][THERMAL ? j : 0];
             }
         }
     }
@@ -140,14 +195,14 @@ __global__ __launch_bounds__(NT) void k_step_deep(Dom d, DeepPlan p, int C, int 
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         int x, y;
-        ring[r] = deep_node(X, Y, C, (int)threadIdx.x + r * NT, x, y);
-        if (ring[r] >= C || x >= X.last(C) || y >= Y.last(C)) {
+        ring[r] = deep_node(F.X, F.Y, C, (int)threadIdx.x + r * NT, x, y);
+        if (ring[r] >= C || x >= F.X.last(C) || y >= F.Y.last(C)) {
             ring[r] = C;   // no node left for this thread
             continue;
         }
-        const int gx = wrapped(x, d.nx), gy = wrapped(y, d.ny);
+        const int gx = F.wrapped(x, d.nx), gy = F.wrapped(y, d.ny);
         o[r] = (uint32_t)(gy * d.pitch + gx);
-        own[r] = (y - fy0) * fw + (x - fx0);
+        own[r] = (y - F.y0) * F.s + (x - F.x0);
         c[r] = med.cell(d, med.load(o[r] * 4));
         // the node that the links are gathered for: on an on-node wall its inner neighbour
         int bx = gx, by = gy;
@@ -158,25 +213,14 @@ __global__ __launch_bounds__(NT) void k_step_deep(Dom d, DeepPlan p, int C, int 
             wx[r] = gx;
             wy[r] = gy;
         }
-        // its LDS row and column and those beside it; an axis that one tile covers wraps
-        const int cx = x + (bx - gx) - fx0, cy = y + (by - gy) - fy0;
-        const bool xl = bx == 0, xr = bx == d.nx - 1, yl = by == 0, yr = by == d.ny - 1;
-        const bool wx_ = p.tiles_x == 1 && per_x, wy_ = p.tiles_y == 1 && per_y;
-        const int colm = xl && wx_ ? d.nx - 1 : cx - 1, colp = xr && wx_ ? 0 : cx + 1;
-        const int row0 = cy * fw, rowm = (yl && wy_ ? d.ny - 1 : cy - 1) * fw, rowp = (yr && wy_ ? 0 : cy + 1) * fw;
-        const bool outl = xl && !per_x, outr = xr && !per_x, outb = yl && !per_y, outt = yr && !per_y;
-        auto locate = [&](int ex, int ey, int plane, int oplane) -> int {
-            const bool out = (ex > 0 && outl) || (ex < 0 && outr) || (ey > 0 && outb) || (ey < 0 && outt);
-            const int at = (ey > 0 ? rowm : (ey < 0 ? rowp : row0)) + (ex > 0 ? colm : (ex < 0 ? colp : cx));
-            return out ? oplane * CAP + row0 + cx : plane * CAP + at;
-        };
-        top[r] = outt;
+        const DeepLinks at(F, bx, by, x + (bx - gx) - F.x0, y + (by - gy) - F.y0);
+        top[r] = at.outt;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) src[r][i] = locate(EX[i], EY[i], i, OPP[i]);
+        for (int i = 0; i < 8; ++i) src[r][i] = at.source(EX[i], EY[i], i, OPP[i], CAP);
         if (THERMAL) {
 #pragma unroll
-            for (int j = 0; j < 5; ++j) gsrc[r][j] = locate(TXv[j], TYv[j], j, TOPP[j]);
-            kind[r] = (outl ? 2u << 2 : 0u) | (outr ? 3u << 6 : 0u);   // links 1 and 3
+            for (int j = 0; j < 5; ++j) gsrc[r][j] = at.source(TXv[j], TYv[j], j, TOPP[j], CAP);
+            kind[r] = (at.outl ? 2u << 2 : 0u) | (at.outr ? 3u << 6 : 0u);   // links 1 and 3
         }
     }
 
@@ -216,6 +260,17 @@ __global__ __launch_bounds__(NT) void k_step_deep(Dom d, DeepPlan p, int C, int 
             }
             float ux, uy, n7, n8, dT;
             node_update<THERMAL>(d, c[r], f, g, ux, uy, n7, n8, dT);
+            if (REC && ring[r] == 0) {
+                const uint32_t pb4 = (uint32_t)(d.plane * 4);
+                const BufRes rec = buf_res(d.urec + (int64_t)k * 5 * d.plane, 5 * pb4);
+                BufIO<float>::st(rec, o[r] * 4, 0u, ux);
+                BufIO<float>::st(rec, o[r] * 4, pb4, uy);
+                if (d.rec_stress) {
+                    BufIO<float>::st(rec, o[r] * 4, 2 * pb4, n7);
+                    BufIO<float>::st(rec, o[r] * 4, 3 * pb4, n8);
+                }
+                if (THERMAL) BufIO<float>::st(rec, o[r] * 4, 4 * pb4, dT);
+            }
             if (k < C - 1) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) to[i * CAP + own[r]] = (float)(S)f[i];
@@ -251,11 +306,25 @@ static int deep_width(int n, int tiles, bool periodic, int C) {
     return !periodic && w > n ? n : w;
 }
 
-// (0 for a frame beyond every compiled one)
+// Row stride of the frames in LDS: their width, except that a ring's columns would
+// meet in one or two LDS banks at a stride of 32 or 33 (256^2 cavity, eight cycles:
+// 1.80 us per step with rows of 32, 1.50 with 34; 200^2, ten: 1.88 with 33, 1.35).
+static int deep_stride(const Dom &d, const DeepPlan &p, int C) {
+    const int w = deep_width(d.nx, p.tiles_x, d.bc_x == BC_PERIODIC, C);
+    return p.tiles_x > 1 && w % 32 < 2 ? w - w % 32 + 2 : w;
+}
+
+// LDS nodes of a frame (0 for one beyond every compiled size)
 static int deep_frame(const Dom &d, const DeepPlan &p, int C) {
-    const int64_t n = (int64_t)deep_width(d.nx, p.tiles_x, d.bc_x == BC_PERIODIC, C) *
-                      deep_width(d.ny, p.tiles_y, d.bc_y == BC_PERIODIC, C);
+    const int64_t n = (int64_t)deep_stride(d, p, C) * deep_width(d.ny, p.tiles_y, d.bc_y == BC_PERIODIC, C);
     return n <= (d.thermal ? DEEP_CAP_HEAT : DEEP_CAP) ? (int)n : 0;
+}
+
+// (the kernel wraps a ring around a periodic axis once)
+static bool deep_fits(const Dom &d, const DeepPlan &p, int C) {
+    if ((p.tiles_x > 1 && d.bc_x == BC_PERIODIC && C > d.nx) || (p.tiles_y > 1 && d.bc_y == BC_PERIODIC && C > d.ny))
+        return false;
+    return C >= 1 && p.tiles_x >= 1 && p.tiles_y >= 1 && p.tiles_x <= d.nx && p.tiles_y <= d.ny;
 }
 
 // Where the deep pass is taken, and its tiles (us per step, other pass against
@@ -267,22 +336,26 @@ static int deep_frame(const Dom &d, const DeepPlan &p, int C) {
 //     double a wavefront's arithmetic (7.6 against 1.10; 24 x 32 alone 1.67, tiled
 //     1.12). 1024 cycles at most, so that no launch holds the chip for long.
 //   * Else one tile per CU, as square as they come, and the most cycles up to 10
-//     that its frame holds (128^2 lid cavity: 2.5 against 1.03, 256^2 2.6 against
-//     1.50, 512^2 3.1 against 2.5, 600 x 500 3.8 against 3.1; convection 200^2 3.2
-//     against 2.0, 450^2 4.2 against 3.6). More cycles lose to the ring (128^2: 8
+//     that its frame holds (128^2 lid cavity: 2.5 against 0.98, 256^2 2.6 against
+//     1.42, 512^2 3.1 against 2.5, 600 x 500 3.8 against 3.1; convection 200^2 3.2
+//     against 1.9, 450^2 4.2 against 3.6). More cycles lose to the ring (128^2: 8
 //     cycles 1.03, 12 1.22, 16 1.20). With fewer than five, or in two rounds of
 //     tiles, the other passes are as fast or faster (600^2 3.8 against 3.8; 850^2
 //     5.7 against 6.7; convection 512^2 4.3 against 5.0).
 //   * With on-node walls, whose other pass takes one cycle, up to five rounds
-//     (convection 200^2 9.5 against 2.4, 1000^2 22.7 against 17.4; cavity 512^2 7.1
+//     (convection 200^2 9.5 against 2.3, 1000^2 22.7 against 17.4; cavity 512^2 7.1
 //     against 3.2, 1000^2 14.1 against 11.3).
+//   * Where a frame of one node per thread holds seven cycles, no more of them in a
+//     larger frame (200^2 cavity: nine 1.22, ten 1.35; 240^2: eight 1.42, ten 1.53;
+//     256^2: seven 1.42, nine 1.47; 300^2: six 1.83, ten 1.68).
 constexpr int DEEP_MOST_CYCLES = 10, DEEP_LEAST_CYCLES = 5;
+constexpr int DEEP_ONE_NODE = 1024, DEEP_ONE_NODE_CYCLES = 7;
 
 bool deep_plan(const Dom &d, DeepPlan *plan, int *cycles) {
     constexpr int CUS = 256;
     const bool nee = d.bc_x == BC_NEE || d.bc_y == BC_NEE;
     if ((int64_t)d.nx * d.ny <= (nee ? 512 : (d.thermal ? 640 : 800))) {
-        *plan = DeepPlan{1, 1};
+        *plan = DeepPlan{1, 1, 0};
         *cycles = 1024;
         return true;
     }
@@ -291,27 +364,31 @@ bool deep_plan(const Dom &d, DeepPlan *plan, int *cycles) {
         int tx = (int)(std::sqrt((double)wgs * d.nx / d.ny) + 0.5);
         tx = std::min(std::max(tx, 1), std::min(d.nx, wgs));
         const int ty = std::min(wgs / tx, d.ny);
-        const DeepPlan p{tx, ty};
-        for (int C = DEEP_MOST_CYCLES; C >= DEEP_LEAST_CYCLES; --C) {
-            // the kernel wraps a ring around a periodic axis once
-            if ((tx > 1 && d.bc_x == BC_PERIODIC && C > d.nx) || (ty > 1 && d.bc_y == BC_PERIODIC && C > d.ny)) continue;
-            if (!deep_frame(d, p, C)) continue;
+        const DeepPlan p{tx, ty, 0};
+        int best = 0;
+        for (int C = DEEP_LEAST_CYCLES; C <= DEEP_MOST_CYCLES; ++C) {
+            if (!deep_fits(d, p, C) || !deep_frame(d, p, C)) continue;
+            if (best >= DEEP_ONE_NODE_CYCLES && deep_frame(d, p, best) <= DEEP_ONE_NODE && deep_frame(d, p, C) > DEEP_ONE_NODE) break;
+            best = C;
+        }
+        if (best > 0) {
             *plan = p;
-            *cycles = C;
+            *cycles = best;
             return true;
         }
     }
     return false;
 }
 
-template <typename S, int MK, bool THERMAL, bool NEE>
+template <typename S, int MK, bool THERMAL, bool NEE, bool REC>
 static hipError_t launch_deep_t(const Dom &d, const DeepPlan &p, int C, int direct, hipStream_t st) {
     const int n = deep_frame(d, p, C);
     if (n == 0) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(p.tiles_x * p.tiles_y));
+    const DeepPlan q{p.tiles_x, p.tiles_y, deep_stride(d, p, C)};
 #define MRT_DEEP(CAP, NT) \
     if (n <= CAP) { \
-        hipLaunchKernelGGL((k_step_deep<S, MK, THERMAL, NEE, CAP, NT>), grid, dim3(NT), 0, st, d, p, C, direct); \
+        hipLaunchKernelGGL((k_step_deep<S, MK, THERMAL, NEE, REC, CAP, NT>), grid, dim3(NT), 0, st, d, q, C, direct); \
         return hipGetLastError(); \
     }
     MRT_DEEP(512, 512)
@@ -326,19 +403,27 @@ template <typename S, int MK>
 static hipError_t launch_deep_mk(const Dom &d, const DeepPlan &p, int C, int direct, hipStream_t st) {
     const bool nee = d.bc_x == BC_NEE || d.bc_y == BC_NEE;
     if (d.thermal)
-        return nee ? launch_deep_t<S, MK, true, true>(d, p, C, direct, st) : launch_deep_t<S, MK, true, false>(d, p, C, direct, st);
-    return nee ? launch_deep_t<S, MK, false, true>(d, p, C, direct, st) : launch_deep_t<S, MK, false, false>(d, p, C, direct, st);
+        return nee ? launch_deep_t<S, MK, true, true, false>(d, p, C, direct, st)
+                   : launch_deep_t<S, MK, true, false, false>(d, p, C, direct, st);
+    return nee ? launch_deep_t<S, MK, false, true, false>(d, p, C, direct, st)
+               : launch_deep_t<S, MK, false, false, false>(d, p, C, direct, st);
 }
 
 hipError_t launch_step_deep(const Dom &d, int storage, const DeepPlan &p, int C, bool direct, hipStream_t st) {
-    if ((p.tiles_x > 1 && d.bc_x == BC_PERIODIC && C > d.nx) || (p.tiles_y > 1 && d.bc_y == BC_PERIODIC && C > d.ny))
-        return hipErrorInvalidValue;
-    if (C < 1 || p.tiles_x < 1 || p.tiles_y < 1 || p.tiles_x > d.nx || p.tiles_y > d.ny) return hipErrorInvalidValue;
+    if (!deep_fits(d, p, C)) return hipErrorInvalidValue;
     const bool uniform = medium_kind(d) == MK_UNIFORM;
     const int dir = direct ? 1 : 0;
     if (storage == ST_F32)
         return uniform ? launch_deep_mk<float, MK_UNIFORM>(d, p, C, dir, st) : launch_deep_mk<float, MK_ANY>(d, p, C, dir, st);
     return uniform ? launch_deep_mk<_Float16, MK_UNIFORM>(d, p, C, dir, st) : launch_deep_mk<_Float16, MK_ANY>(d, p, C, dir, st);
+}
+
+// FP32, no on-node walls: what the adjoint takes.
+hipError_t launch_step_deep_rec(const Dom &d, const DeepPlan &p, int C, bool direct, hipStream_t st) {
+    if (!deep_fits(d, p, C) || d.bc_x == BC_NEE || d.bc_y == BC_NEE) return hipErrorInvalidValue;
+    const int dir = direct ? 1 : 0;
+    return d.thermal ? launch_deep_t<float, MK_ANY, true, false, true>(d, p, C, dir, st)
+                     : launch_deep_t<float, MK_ANY, false, false, true>(d, p, C, dir, st);
 }
 
 }  // namespace mrt
