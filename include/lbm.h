@@ -334,8 +334,8 @@ int lbm_set_time_blocking(lbm_ctx *c, int32_t cycles_per_pass);
  * by strip passes of six and four cycles. The mode reported below fills in
  * where they do not fit. A mode set here (and for the small ones a tile set by
  * lbm_set_two_cycle_tile or, with on-node walls, a launch shape) replaces
- * them. Deep passes run an adjoint's recomputation and its backward sweep too.
- * Same bits as every other pass. */
+ * them. Deep passes run an adjoint's recomputation and
+ * its backward sweep too, and the tangent. Same bits as every other pass. */
 
 /* Current cycles per pass, and the workgroup size, tile rows (tiles are 64
  * nodes wide) and grid size of the multi-cycle pass it runs: the four-cycle

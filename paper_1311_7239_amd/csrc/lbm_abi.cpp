@@ -667,7 +667,7 @@ int lbm_create(const lbm_desc *d, const float *phi, const float *kappa, void *wo
     if (d->thermal.enabled) c->tb_rows = 8;
     if (d->storage == LBM_FP16_DEV) c->sched = Schedule{64, 2, 2, 1};
     if (buffer_below_4gib(L)) {
-        (void)deep_plan(D.dom, &c->deep, &c->deep_cycles);
+        (void)deep_plan(D.dom, INT64_MAX, &c->deep, &c->deep_cycles);
         c->strip = strip_domain(D.dom, d->storage == LBM_FP16_DEV ? ST_F16 : ST_F32);
     }
     hipError_t e = init_domain(D, 0, phi, kappa, c->stream);
@@ -1642,10 +1642,11 @@ int backward_impl(lbm_ctx *c, const float *dL_du, float *dL_dphi, float *dL_dkap
     double *acc_step = acc ? acc + 4 * adjoint_theta_offset(d.nx, d.ny, 1) : nullptr;
     double *acc_step2 = acc ? acc + 4 * adjoint_theta_offset(d.nx, d.ny, 2) : nullptr;
     hipStream_t st = c->stream;
-    // small domains: deep passes both ways (the same bits again)
+    // Small domains: deep passes both ways (the same bits again). A parameter gradient
+    // has a slot per tile of the reverse pass: flat domains with few take fewer tiles.
     DeepPlan adeep{};
     int adeep_cycles = 0;
-    if (c->deep_cycles > 0 && !adjoint_deep_plan(D.dom, (int64_t)L.theta_slots, &adeep, &adeep_cycles)) adeep_cycles = 0;
+    if (c->deep_cycles > 0) (void)deep_plan(D.dom, (int64_t)L.theta_slots, &adeep, &adeep_cycles);
 
     hipError_t e = hipSuccess;
     if (acc) e = launch_fill_zero(acc, sizeof(double) * 4 * (L.theta_slots + 1), st);
@@ -1775,19 +1776,53 @@ extern "C" int lbm_tangent(lbm_ctx *c, const float *dphi, const double *dtheta, 
     if (e != hipSuccess) return device_fail(c, e, "tangent set-up");
     const float dnu = dtheta ? (float)dtheta[0] : 0.0f, dax = dtheta ? (float)dtheta[1] : 0.0f;
     const float day = dtheta ? (float)dtheta[2] : 0.0f, dU = dtheta ? (float)dtheta[3] : 0.0f;
-    int p = 0;
-    for (int64_t t = 0; t <= T; ++t) {
-        Dom ds = D.dom, dtn = D.dom;
+    int p = 0, q = 0;   // buffers of the state and of its tangent
+    auto state = [&]() -> Dom {
+        Dom ds = D.dom;
         ds.fin = D.base + L.off_rf[p];
         ds.fout = D.base + L.off_rf[p ^ 1];
-        dtn.fin = tan[p];
-        dtn.fout = tan[p ^ 1];
+        return ds;
+    };
+    auto tangent = [&]() -> Dom {
+        Dom dtn = D.dom;
+        dtn.fin = tan[q];
+        dtn.fout = tan[q ^ 1];
         dtn.lid6 = dU / 6.0f;
+        return dtn;
+    };
+    int64_t t0 = 0;
+    if (c->deep_cycles > 0) {
+        // small domains: a segment's state in deep passes that record, then its tangent
+        // in deep passes that read the records
+        float *urec = (float *)(D.base + L.off_urec);
+        const size_t rstride = 5 * (size_t)L.plane;
+        for (; t0 < T;) {
+            const int64_t t1 = std::min<int64_t>(t0 + d.ckpt_every, T);
+            for (int64_t t = t0, n; t < t1; t += n, p ^= 1) {
+                n = deep_cycles_of(c->deep_cycles, t1 - t);
+                Dom ds = state();
+                ds.urec = urec + (size_t)(t - t0) * rstride;
+                ds.rec_stress = 1;
+                e = launch_step_deep_rec(ds, c->deep, (int)n, t == 0, st);
+                if (e != hipSuccess) return device_fail(c, e, "recompute step");
+            }
+            for (int64_t t = t0, n; t < t1; t += n, q ^= 1) {
+                n = deep_cycles_of(c->deep_cycles, t1 - t);
+                e = launch_tangent_deep(tangent(), c->deep, (int)n, t == 0, urec + (size_t)(t - t0) * rstride, dphi_p,
+                                        dnu, dax, day, st);
+                if (e != hipSuccess) return device_fail(c, e, "tangent step");
+            }
+            t0 = t1;
+        }
+    }
+    for (int64_t t = t0; t <= T; ++t) {
+        const Dom ds = state(), dtn = tangent();
         const Source src = t == 0 ? SRC_DIRECT : SRC_GATHER;
         if (t == T) e = launch_tangent_u(ds, dtn, src, dphi_p, dnu, dax, day, du, st);
         else e = launch_tangent_step(ds, dtn, src, dphi_p, dnu, dax, day, st);
         if (e != hipSuccess) return device_fail(c, e, "tangent step");
         p ^= 1;
+        q ^= 1;
     }
     return LBM_OK;
 }

@@ -1136,147 +1136,162 @@ hipError_t launch_adjoint_step_thermal(const Dom &d, const float *lam_in, float 
 // The reverse mode of the deep pass: C backward steps per launch for domains that
 // leave most of the chip idle, on the same tiles and rings (the transposed gather
 // pulls from x + e instead of x - e, so it is the same frame with the directions
-// turned round). One node per thread: its LDS sources, its cell, the derivatives
-// of its drag and its running medium gradient stay in registers for the whole
-// pass, the next step's record is loaded before this step's collision. The
-// gradient adds one step after the other, so the result is bitwise that of single
-// steps; the parameter sums, which run over many steps here, are in FP64.
+// turned round). A node's LDS sources, its cell, the derivatives of its drag and
+// its running medium gradient stay in registers for the whole pass, the next
+// step's record is loaded before this step's collision. The gradient adds one step
+// after the other, so the result is bitwise that of single steps; the parameter
+// sums, which run over many steps here, are in FP64.
 //
 // What bounds it: a launch, the load and the store of the frame (about 5 us per
-// launch), and the issue of one wavefront of nodes per 64 threads in each step. A
-// whole backward pass, with its recomputation (segments of 50 steps, us per step):
-// 320^2 with the thermal model and parameter gradients 11.1 -> 6.3, of which 4.0
-// here (7.2 in two-step tiles); 160^2 isothermal 7.6 -> 2.6, 400^2 8.2 -> 5.6.
-template <bool THETA, bool THERMAL, int NT>
+// launch), and the issue of the wavefronts of nodes in each step. A whole
+// backward pass with its recomputation (segments of 50 steps, us per step, tiles
+// against deep passes): heat 320^2 with parameter gradients 11.1 against 6.1, 450^2
+// 12.3 against 9.4; isothermal 100^2 7.5 against 2.3, 400^2 8.2 against 4.5, 512^2
+// 8.6 against 6.3. The forward pass's tiles and cycles are as good as any here
+// (heat 320^2: ten 6.1, eight 6.0, five 6.3, three 7.3; 512^2: six 6.3, four 6.9).
+template <bool THETA, bool THERMAL, int CAP, int NT>
 __global__ __launch_bounds__(NT) void k_adjoint_deep(Dom d, DeepPlan p, int C, const float *__restrict__ lam_in,
                                                      float *__restrict__ lam_out, const float *__restrict__ lamg_in,
                                                      float *__restrict__ lamg_out, const float *__restrict__ u_t,
                                                      float *__restrict__ gphi, float *__restrict__ gkappa,
                                                      double *__restrict__ acc) {
-    constexpr int CAP = NT;
+    constexpr int R = (CAP + NT - 1) / NT;
     __shared__ float lds[2 * 8 * CAP];
     __shared__ float ldsg[THERMAL ? 2 * 5 * CAP : 1];
     const DeepFrame F(d, p, C);
     const uint32_t pb4 = (uint32_t)(d.plane * 4);
     const BufRes rg = buf_res(gphi, pb4), rgk = buf_res(gkappa, gkappa ? pb4 : 0u);
     const MediumSrc<MK_ANY> med(d);
-    const int s = (int)threadIdx.x;
     ThetaSumOf<double> ts{0.0, 0.0, 0.0, 0.0};   // over many steps
 
-    if (s < F.n) {
+    // the frame's a(t + 1) into the first LDS buffer
+    {
         const BufRes rl = buf_res(lam_in, 8 * pb4), rlg = buf_res(THERMAL ? lamg_in : nullptr, THERMAL ? 5 * pb4 : 0u);
-        int at;
-        const uint32_t v = F.offset(s, 1.0f / (float)F.w, d.pitch, at) * 4;
-        float a[8], ag[5];
+        const float inv = 1.0f / (float)F.w;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) a[i] = BufIO<float>::ld(rl, v, (uint32_t)i * pb4);
-        if (THERMAL) {
+        for (int r = 0; r < R; ++r) {
+            const int s = (int)threadIdx.x + r * NT;
+            if (s >= F.n) continue;
+            int at;
+            const uint32_t v = F.offset(s, inv, d.pitch, at) * 4;
+            float a[8], ag[5];
 #pragma unroll
-            for (int j = 0; j < 5; ++j) ag[j] = BufIO<float>::ld(rlg, v, (uint32_t)j * pb4);
-        }
+            for (int i = 0; i < 8; ++i) a[i] = BufIO<float>::ld(rl, v, (uint32_t)i * pb4);
+            if (THERMAL) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) lds[i * CAP + at] = a[i];
-        if (THERMAL) {
+                for (int j = 0; j < 5; ++j) ag[j] = BufIO<float>::ld(rlg, v, (uint32_t)j * pb4);
+            }
 #pragma unroll
-            for (int j = 0; j < 5; ++j) ldsg[j * CAP + at] = ag[j];
+            for (int i = 0; i < 8; ++i) lds[i * CAP + at] = a[i];
+            if (THERMAL) {
+#pragma unroll
+                for (int j = 0; j < 5; ++j) ldsg[j * CAP + at] = ag[j];
+            }
         }
     }
 
-    int x, y, src[8], gsrc[5], own = 0;
-    int ring = deep_node(F.X, F.Y, C, s, x, y);
-    uint32_t o4 = 0, minus = 0;   // minus: D2Q5 links that come back from an isothermal wall
-    bool top = false;
-    Cell c;
-    MediumDerivs md{0.0f, 0.0f, 0.0f};
-    float gp = 0.0f, gk = 0.0f;
     struct Rec {
         float ux, uy, n7, n8, dT;
     };
-    auto record = [&](int k) -> Rec {
-        const BufRes r = buf_res(u_t - (int64_t)k * 5 * d.plane, 5 * pb4);
-        return Rec{BufIO<float>::ld(r, o4, 0u), BufIO<float>::ld(r, o4, pb4),
-                   THETA ? BufIO<float>::ld(r, o4, 2 * pb4) : 0.0f, THETA ? BufIO<float>::ld(r, o4, 3 * pb4) : 0.0f,
-                   THERMAL ? BufIO<float>::ld(r, o4, 4 * pb4) : 0.0f};
+    int ring[R], src[R][8], gsrc[R][THERMAL ? 5 : 1], own[R];
+    uint32_t o4[R], minus[R];   // minus: D2Q5 links that come back from an isothermal wall
+    bool top[R];
+    Cell c[R];
+    MediumDerivs md[R];
+    float gp[R], gk[R];
+    Rec next[R];
+    auto record = [&](int k, uint32_t o) -> Rec {
+        const BufRes q = buf_res(u_t - (int64_t)k * 5 * d.plane, 5 * pb4);
+        return Rec{BufIO<float>::ld(q, o, 0u), BufIO<float>::ld(q, o, pb4),
+                   THETA ? BufIO<float>::ld(q, o, 2 * pb4) : 0.0f, THETA ? BufIO<float>::ld(q, o, 3 * pb4) : 0.0f,
+                   THERMAL ? BufIO<float>::ld(q, o, 4 * pb4) : 0.0f};
     };
-    Rec next{0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    if (ring >= C || x >= F.X.last(C) || y >= F.Y.last(C)) {
-        ring = C;   // no node left for this thread
-    } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        int x, y;
+        ring[r] = deep_node(F.X, F.Y, C, (int)threadIdx.x + r * NT, x, y);
+        if (ring[r] >= C || x >= F.X.last(C) || y >= F.Y.last(C)) {
+            ring[r] = C;   // no node left for this thread
+            continue;
+        }
         const int gx = F.wrapped(x, d.nx), gy = F.wrapped(y, d.ny);
-        o4 = (uint32_t)(gy * d.pitch + gx) * 4;
-        own = (y - F.y0) * F.s + (x - F.x0);
-        next = record(0);
-        const CellRaw raw = med.load(o4);
-        c = med.cell(d, raw);
-        if (ring == 0) {
-            md = medium_derivs(d, c, raw.kappa);
-            gp = BufIO<float>::ld(rg, o4, 0u);
-            gk = gkappa ? BufIO<float>::ld(rgk, o4, 0u) : 0.0f;
+        o4[r] = (uint32_t)(gy * d.pitch + gx) * 4;
+        own[r] = (y - F.y0) * F.s + (x - F.x0);
+        next[r] = record(0, o4[r]);
+        const CellRaw raw = med.load(o4[r]);
+        c[r] = med.cell(d, raw);
+        if (ring[r] == 0) {
+            md[r] = medium_derivs(d, c[r], raw.kappa);
+            gp[r] = BufIO<float>::ld(rg, o4[r], 0u);
+            gk[r] = gkappa ? BufIO<float>::ld(rgk, o4[r], 0u) : 0.0f;
         }
         const DeepLinks at(F, gx, gy, x - F.x0, y - F.y0);
-        top = d.bc_y == BC_WALLS && gy == d.ny - 1;
+        top[r] = d.bc_y == BC_WALLS && gy == d.ny - 1;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) src[i] = at.source(-EX[i], -EY[i], i, OPP[i], CAP);
+        for (int i = 0; i < 8; ++i) src[r][i] = at.source(-EX[i], -EY[i], i, OPP[i], CAP);
         if (THERMAL) {
 #pragma unroll
-            for (int j = 0; j < 5; ++j) gsrc[j] = at.source(-TXv[j], -TYv[j], j, TOPP[j], CAP);
-            minus = (at.outr ? 1u << 1 : 0u) | (at.outl ? 1u << 3 : 0u);
+            for (int j = 0; j < 5; ++j) gsrc[r][THERMAL ? j : 0] = at.source(-TXv[j], -TYv[j], j, TOPP[j], CAP);
+            minus[r] = (at.outr ? 1u << 1 : 0u) | (at.outl ? 1u << 3 : 0u);
         }
     }
 
     auto step = [&](int k, const float *from, const float *fromg, float *to, float *tog) {
         lds_barrier();
-        if (ring > C - 1 - k) return;
-        const Rec u = next;
-        if (k + 1 < C) next = record(k + 1);
-        float b[8], bg[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f}, a[8], ag[5], ubx = 0.0f, uby = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) b[i] = from[src[i]];
-        if (THERMAL) {
+        for (int r = 0; r < R; ++r) {
+            if (ring[r] > C - 1 - k) continue;
+            const Rec u = next[r];
+            if (k + 1 < C) next[r] = record(k + 1, o4[r]);
+            float b[8], bg[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f}, a[8], ag[5], ubx = 0.0f, uby = 0.0f;
 #pragma unroll
-            for (int j = 0; j < 5; ++j) {
-                const float v = fromg[gsrc[j]];
-                bg[j] = (minus >> j) & 1u ? -v : v;
-            }
-            thermal_collide_adjoint(bg, d, u.ux, u.uy, u.dT, ag, ubx, uby);
-        }
-        const float ay = THERMAL ? d.ay + d.gbeta * u.dT : d.ay;
-        ParamBar pb;
-        collide_adjoint(b, d, c, c.phi * d.ax, c.phi * ay, u.ux, u.uy, u.n7, u.n8, a, pb, ubx, uby);
-        const float Tb = THERMAL ? c.phi * d.gbeta * pb.pay : 0.0f;
-        if (ring == 0) {
-            float p1, k1;
-            medium_gradient(d, c, md, pb, d.ax, ay, p1, k1);
-            gp += p1;
-            if (gkappa) gk += k1;
-            if (THETA) {
-                ThetaSum one{0.0f, 0.0f, 0.0f, 0.0f};
-                theta_add(d, c, pb, one);
-                if (top) one.lid = lid_share(d, d.ny - 1, from[6 * CAP + own], from[7 * CAP + own]);
-                ts.nu += one.nu;
-                ts.ax += one.ax;
-                ts.ay += one.ay;
-                ts.lid += one.lid;
-            }
-        }
-        if (k < C - 1) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) to[i * CAP + own] = a[i];
+            for (int i = 0; i < 8; ++i) b[i] = from[src[r][i]];
             if (THERMAL) {
 #pragma unroll
-                for (int j = 0; j < 5; ++j) tog[j * CAP + own] = ag[j] + Tb;
+                for (int j = 0; j < 5; ++j) {
+                    const float v = fromg[gsrc[r][THERMAL ? j : 0]];
+                    bg[j] = (minus[r] >> j) & 1u ? -v : v;
+                }
+                thermal_collide_adjoint(bg, d, u.ux, u.uy, u.dT, ag, ubx, uby);
             }
-            return;
-        }
-        const BufRes rl = buf_res(lam_out, 8 * pb4), rlg = buf_res(THERMAL ? lamg_out : nullptr, THERMAL ? 5 * pb4 : 0u);
+            const float ay = THERMAL ? d.ay + d.gbeta * u.dT : d.ay;
+            ParamBar pb;
+            collide_adjoint(b, d, c[r], c[r].phi * d.ax, c[r].phi * ay, u.ux, u.uy, u.n7, u.n8, a, pb, ubx, uby);
+            const float Tb = THERMAL ? c[r].phi * d.gbeta * pb.pay : 0.0f;
+            if (ring[r] == 0) {
+                float p1, k1;
+                medium_gradient(d, c[r], md[r], pb, d.ax, ay, p1, k1);
+                gp[r] += p1;
+                if (gkappa) gk[r] += k1;
+                if (THETA) {
+                    ThetaSum one{0.0f, 0.0f, 0.0f, 0.0f};
+                    theta_add(d, c[r], pb, one);
+                    if (top[r]) one.lid = lid_share(d, d.ny - 1, from[6 * CAP + own[r]], from[7 * CAP + own[r]]);
+                    ts.nu += one.nu;
+                    ts.ax += one.ax;
+                    ts.ay += one.ay;
+                    ts.lid += one.lid;
+                }
+            }
+            if (k < C - 1) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) BufIO<float>::st(rl, o4, (uint32_t)i * pb4, a[i]);
-        if (THERMAL) {
+                for (int i = 0; i < 8; ++i) to[i * CAP + own[r]] = a[i];
+                if (THERMAL) {
 #pragma unroll
-            for (int j = 0; j < 5; ++j) BufIO<float>::st(rlg, o4, (uint32_t)j * pb4, ag[j] + Tb);
+                    for (int j = 0; j < 5; ++j) tog[j * CAP + own[r]] = ag[j] + Tb;
+                }
+            } else {
+                const BufRes rl = buf_res(lam_out, 8 * pb4), rlg = buf_res(THERMAL ? lamg_out : nullptr, THERMAL ? 5 * pb4 : 0u);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) BufIO<float>::st(rl, o4[r], (uint32_t)i * pb4, a[i]);
+                if (THERMAL) {
+#pragma unroll
+                    for (int j = 0; j < 5; ++j) BufIO<float>::st(rlg, o4[r], (uint32_t)j * pb4, ag[j] + Tb);
+                }
+                BufIO<float>::st(rg, o4[r], 0u, gp[r]);
+                if (gkappa) BufIO<float>::st(rgk, o4[r], 0u, gk[r]);
+            }
         }
-        BufIO<float>::st(rg, o4, 0u, gp);
-        if (gkappa) BufIO<float>::st(rgk, o4, 0u, gk);
     };
     float *ldsB = lds + 8 * CAP, *ldsgB = ldsg + (THERMAL ? 5 * CAP : 0);
     for (int k = 0; k < C; k += 2) {
@@ -1286,55 +1301,26 @@ __global__ __launch_bounds__(NT) void k_adjoint_deep(Dom d, DeepPlan p, int C, c
     if (THETA) block_theta_add<NT>(ts, acc + 4 * (int64_t)blockIdx.x);
 }
 
-// Where it is taken and its tiles: as the forward pass (one workgroup for the
-// whole domain where that pass uses one, else a tile per CU), but frames of one node
-// per thread only, and the most steps up to ten that those hold, from three on (320^2
-// with heat, 400 nodes a tile: four steps 6.7, five 6.3; 160^2: five 4.5, eight
-// 4.3, ten 4.1). A parameter gradient needs a slot per tile: narrow or flat
-// domains with fewer take fewer tiles.
-constexpr int ADJ_DEEP_CAP = 1024, ADJ_DEEP_MOST = 10, ADJ_DEEP_LEAST = 3;
-
-bool adjoint_deep_plan(const Dom &d, int64_t slots, DeepPlan *plan, int *cycles) {
-    const int64_t nodes = (int64_t)d.nx * d.ny;
-    if (nodes <= (d.thermal ? 640 : 800)) {
-        *plan = DeepPlan{1, 1, 0};
-        *cycles = 1024;
-        return slots >= 1;
-    }
-    const int wgs = (int)std::min<int64_t>(256, slots);
-    if (wgs < 1) return false;
-    int tx = (int)(std::sqrt((double)wgs * d.nx / d.ny) + 0.5);
-    tx = std::min(std::max(tx, 1), std::min(d.nx, wgs));
-    const DeepPlan p{tx, std::min(wgs / tx, d.ny), 0};
-    for (int C = ADJ_DEEP_MOST; C >= ADJ_DEEP_LEAST; --C) {
-        const int n = deep_fits(d, p, C) ? deep_frame(d, p, C) : 0;
-        if (n == 0 || n > ADJ_DEEP_CAP) continue;
-        *plan = p;
-        *cycles = C;
-        return true;
-    }
-    return false;
-}
-
 hipError_t launch_adjoint_deep(const Dom &d, const DeepPlan &p, int C, const float *lam_in, float *lam_out,
                                const float *lamg_in, float *lamg_out, const float *u_t, float *gphi, float *gkappa,
                                double *acc, hipStream_t st) {
     const int n = deep_fits(d, p, C) ? deep_frame(d, p, C) : 0;
-    if (n == 0 || n > ADJ_DEEP_CAP || d.bc_x == BC_NEE || d.bc_y == BC_NEE) return hipErrorInvalidValue;
+    if (n == 0 || d.bc_x == BC_NEE || d.bc_y == BC_NEE) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(p.tiles_x * p.tiles_y));
     const DeepPlan q{p.tiles_x, p.tiles_y, deep_stride(d, p, C)};
-#define MRT_ADJD(TH, THERMAL, NT) \
-    hipLaunchKernelGGL((k_adjoint_deep<TH, THERMAL, NT>), grid, dim3(NT), 0, st, d, q, C, lam_in, lam_out, lamg_in, \
-                       lamg_out, u_t, gphi, gkappa, acc)
-#define MRT_ADJD_N(TH, THERMAL) \
+#define MRT_ADJD(TH, THERMAL, CAP, NT) \
+    hipLaunchKernelGGL((k_adjoint_deep<TH, THERMAL, CAP, NT>), grid, dim3(NT), 0, st, d, q, C, lam_in, lam_out, \
+                       lamg_in, lamg_out, u_t, gphi, gkappa, acc)
+#define MRT_ADJD_N(TH, THERMAL, CAP, NT) \
     do { \
-        if (n <= 512) MRT_ADJD(TH, THERMAL, 512); \
-        else MRT_ADJD(TH, THERMAL, 1024); \
+        if (n <= 512) MRT_ADJD(TH, THERMAL, 512, 512); \
+        else if (n <= 1024) MRT_ADJD(TH, THERMAL, 1024, 1024); \
+        else MRT_ADJD(TH, THERMAL, CAP, NT); \
     } while (0)
-    if (d.thermal && acc) MRT_ADJD_N(true, true);
-    else if (d.thermal) MRT_ADJD_N(false, true);
-    else if (acc) MRT_ADJD_N(true, false);
-    else MRT_ADJD_N(false, false);
+    if (d.thermal && acc) MRT_ADJD_N(true, true, DEEP_CAP_HEAT, 768);
+    else if (d.thermal) MRT_ADJD_N(false, true, DEEP_CAP_HEAT, 768);
+    else if (acc) MRT_ADJD_N(true, false, DEEP_CAP, 1024);
+    else MRT_ADJD_N(false, false, DEEP_CAP, 1024);
 #undef MRT_ADJD_N
 #undef MRT_ADJD
     return hipGetLastError();
@@ -1379,30 +1365,29 @@ __device__ __forceinline__ TanIn tangent_inputs(const Dom &d, const Cell &c, flo
     return t;
 }
 
-// Forward mode of one node's collision (Eq. 14 and f+ = M^-1 m+): given f and
-// its tangent ft, returns the tangent of f+.
-__device__ __forceinline__ void collide_tangent(const float f[8], const float ft[8], const Dom &d,
-                                                const Cell &c, float pax, float pay, const TanIn &ti,
-                                                float out[8]) {
-    auto moments = [](const float g[8], float m[8]) {
-        const float a = g[0] + g[2], b = g[1] + g[3], cc = g[4] + g[6], dg = g[5] + g[7];
-        const float x13 = g[0] - g[2], y24 = g[1] - g[3], p57 = g[4] - g[6], q68 = g[5] - g[7];
-        const float pmq = p57 - q68, ppq = p57 + q68;
-        m[0] = (a + b) + (cc + dg);
-        m[1] = (cc + dg) - (a + b);
-        m[2] = x13 + pmq;
-        m[3] = fmaf(-2.0f, x13, pmq);
-        m[4] = y24 + ppq;
-        m[5] = fmaf(-2.0f, y24, ppq);
-        m[6] = a - b;
-        m[7] = cc - dg;
-    };
-    float m[8], dm[8];
-    moments(f, m);
-    moments(ft, dm);
-    // forward quantities, as in collide
-    float ux, uy;
-    velocity(c, fmaf(0.5f, pax, m[2]), fmaf(0.5f, pay, m[4]), ux, uy);
+// m = M g (rows of Eq. 10)
+__device__ __forceinline__ void moments_of(const float g[8], float m[8]) {
+    const float a = g[0] + g[2], b = g[1] + g[3], cc = g[4] + g[6], dg = g[5] + g[7];
+    const float x13 = g[0] - g[2], y24 = g[1] - g[3], p57 = g[4] - g[6], q68 = g[5] - g[7];
+    const float pmq = p57 - q68, ppq = p57 + q68;
+    m[0] = (a + b) + (cc + dg);
+    m[1] = (cc + dg) - (a + b);
+    m[2] = x13 + pmq;
+    m[3] = fmaf(-2.0f, x13, pmq);
+    m[4] = y24 + ppq;
+    m[5] = fmaf(-2.0f, y24, ppq);
+    m[6] = a - b;
+    m[7] = cc - dg;
+}
+
+// Forward mode of one node's collision (Eq. 14 and f+ = M^-1 m+): given the node's
+// velocity and non-equilibrium stress moments n7, n8 (what the collision's Jacobian
+// depends on, never f itself) and the tangent ft of f, returns the tangent of f+.
+__device__ __forceinline__ void collide_tangent(float ux, float uy, float n7, float n8, const float ft[8],
+                                                const Dom &d, const Cell &c, float pax, float pay,
+                                                const TanIn &ti, float out[8]) {
+    float dm[8];
+    moments_of(ft, dm);
     const float umag = hw_sqrt(fmaf(ux, ux, uy * uy));
     const float drag = fmaf(c.cf, umag, c.cd);
     const float Fx = fmaf(-drag, ux, pax), Fy = fmaf(-drag, uy, pay);
@@ -1426,15 +1411,14 @@ __device__ __forceinline__ void collide_tangent(const float f[8], const float ft
     mp[4] = udy + 0.5f * dFy;
     mp[3] = dm[3] - d.s_q * (dm[3] + udx) - d.h_q * dFx;
     mp[5] = dm[5] - d.s_q * (dm[5] + udy) - d.h_q * dFy;
-    const float pxx = (ux * ux - uy * uy) * ip, pxy = ux * uy * ip;
     const float Sxx = 2.0f * (ux * Fx - uy * Fy) * ip, Sxy = (ux * Fy + uy * Fx) * ip;
     const float dpxx = 2.0f * (ux * udx - uy * udy) * ip + (ux * ux - uy * uy) * ti.dip;
     const float dpxy = (udx * uy + ux * udy) * ip + ux * uy * ti.dip;
     const float dSxx = 2.0f * ((udx * Fx + ux * dFx) - (udy * Fy + uy * dFy)) * ip +
                        2.0f * (ux * Fx - uy * Fy) * ti.dip;
     const float dSxy = ((udx * Fy + ux * dFy) + (udy * Fx + uy * dFx)) * ip + (ux * Fy + uy * Fx) * ti.dip;
-    mp[6] = dm[6] - c.s_nu * (dm[6] - dpxx) + c.h_nu * dSxx - ti.ds * ((m[6] - pxx) + 0.5f * Sxx);
-    mp[7] = dm[7] - c.s_nu * (dm[7] - dpxy) + c.h_nu * dSxy - ti.ds * ((m[7] - pxy) + 0.5f * Sxy);
+    mp[6] = dm[6] - c.s_nu * (dm[6] - dpxx) + c.h_nu * dSxx - ti.ds * (n7 + 0.5f * Sxx);
+    mp[7] = dm[7] - c.s_nu * (dm[7] - dpxy) + c.h_nu * dSxy - ti.ds * (n8 + 0.5f * Sxy);
     // f+ tangent = M^T diag(1/8, 1/8, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4) m+ tangent
     const float y[8] = {0.125f * mp[0], 0.125f * mp[1], mp[2] * (1.0f / 6.0f), mp[3] * (1.0f / 12.0f),
                         mp[4] * (1.0f / 6.0f), mp[5] * (1.0f / 12.0f), 0.25f * mp[6], 0.25f * mp[7]};
@@ -1460,16 +1444,128 @@ __global__ __launch_bounds__(ABLOCK) void k_tangent_step(Dom d, Dom dt, int src,
     const int64_t o = (int64_t)y * d.pitch + x;
     const Cell c = load_cell(d, o);
     const TanIn ti = tangent_inputs(d, c, kappa_at(d, o), dphi ? dphi[o] : 0.0f, dnu, dax, day);
-    float fpt[8];
-    collide_tangent(f, ft, d, c, c.phi * d.ax, c.phi * d.ay, ti, fpt);
-    float ux, uy;
-    collide(f, d, c, c.phi * d.ax, c.phi * d.ay, ux, uy);
+    float fpt[8], ux, uy, n7, n8;
+    collide(f, d, c, c.phi * d.ax, c.phi * d.ay, ux, uy, n7, n8);
+    collide_tangent(ux, uy, n7, n8, ft, d, c, c.phi * d.ax, c.phi * d.ay, ti, fpt);
     float *fo = (float *)d.fout, *fto = (float *)dt.fout;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         fo[i * d.plane + o] = f[i];
         fto[i * d.plane + o] = fpt[i];
     }
+}
+
+// The tangent of the deep pass: C tangent steps per launch on its tiles and rings,
+// from the records that the deep recomputation leaves (u and the stress moments of
+// each step): the state itself is neither read nor streamed here. d is the tangent's
+// domain (fin, fout, lid6 as for k_tangent_step), the arithmetic and the bits those of
+// k_tangent_step, which moves the eight planes of f through memory as well, at
+// every step. us per step with the recomputation: 200^2 5.8 -> 3.3, 400^2 9.5 -> 5.4,
+// 512^2 12.8 -> 7.3.
+template <int CAP, int NT>
+__global__ __launch_bounds__(NT) void k_tangent_deep(Dom d, DeepPlan p, int C, int direct, const float *__restrict__ u_t,
+                                                     const float *__restrict__ dphi, float dnu, float dax, float day) {
+    constexpr int R = (CAP + NT - 1) / NT;
+    __shared__ float lds[2 * 8 * CAP];
+    const DeepFrame F(d, p, C);
+    const uint32_t pb4 = (uint32_t)(d.plane * 4);
+    const BufRes rin = buf_res(d.fin, 8 * pb4), rout = buf_res(d.fout, 8 * pb4), rd = buf_res(dphi, dphi ? pb4 : 0u);
+    const MediumSrc<MK_ANY> med(d);
+    {
+        const float inv = 1.0f / (float)F.w;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int s = (int)threadIdx.x + r * NT;
+            if (s >= F.n) continue;
+            int at;
+            const uint32_t v = F.offset(s, inv, d.pitch, at) * 4;
+            float f[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) f[i] = BufIO<float>::ld(rin, v, (uint32_t)i * pb4);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) lds[i * CAP + at] = f[i];
+        }
+    }
+    struct Rec {
+        float ux, uy, n7, n8;
+    };
+    int ring[R], src[R][8], own[R];
+    uint32_t o4[R];
+    bool top[R];
+    Cell c[R];
+    TanIn ti[R];
+    Rec next[R];
+    auto record = [&](int k, uint32_t o) -> Rec {
+        const BufRes q = buf_res(u_t + (int64_t)k * 5 * d.plane, 5 * pb4);
+        return Rec{BufIO<float>::ld(q, o, 0u), BufIO<float>::ld(q, o, pb4), BufIO<float>::ld(q, o, 2 * pb4),
+                   BufIO<float>::ld(q, o, 3 * pb4)};
+    };
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        int x, y;
+        ring[r] = deep_node(F.X, F.Y, C, (int)threadIdx.x + r * NT, x, y);
+        if (ring[r] >= C || x >= F.X.last(C) || y >= F.Y.last(C)) {
+            ring[r] = C;   // no node left for this thread
+            continue;
+        }
+        const int gx = F.wrapped(x, d.nx), gy = F.wrapped(y, d.ny);
+        o4[r] = (uint32_t)(gy * d.pitch + gx) * 4;
+        own[r] = (y - F.y0) * F.s + (x - F.x0);
+        next[r] = record(0, o4[r]);
+        const CellRaw raw = med.load(o4[r]);
+        c[r] = med.cell(d, raw);
+        ti[r] = tangent_inputs(d, c[r], raw.kappa, dphi ? BufIO<float>::ld(rd, o4[r], 0u) : 0.0f, dnu, dax, day);
+        const DeepLinks at(F, gx, gy, x - F.x0, y - F.y0);
+        top[r] = at.outt;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) src[r][i] = at.source(EX[i], EY[i], i, OPP[i], CAP);
+    }
+    auto step = [&](int k, const float *from, float *to) {
+        lds_barrier();
+        const bool as_is = k == 0 && direct;   // the tangent of f(0): nothing to stream
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (ring[r] > C - 1 - k) continue;
+            const Rec u = next[r];
+            if (k + 1 < C) next[r] = record(k + 1, o4[r]);
+            float ft[8], out[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ft[i] = from[as_is ? i * CAP + own[r] : src[r][i]];
+            if (top[r] && !as_is) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (EY[i] < 0) ft[i] = ft[i] + (float)EX[i] * d.lid6;
+            }
+            collide_tangent(u.ux, u.uy, u.n7, u.n8, ft, d, c[r], c[r].phi * d.ax, c[r].phi * d.ay, ti[r], out);
+            if (k < C - 1) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) to[i * CAP + own[r]] = out[i];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) BufIO<float>::st(rout, o4[r], (uint32_t)i * pb4, out[i]);
+            }
+        }
+    };
+    for (int k = 0; k < C; k += 2) {
+        step(k, lds, lds + 8 * CAP);
+        if (k + 1 < C) step(k + 1, lds + 8 * CAP, lds);
+    }
+}
+
+hipError_t launch_tangent_deep(const Dom &dt, const DeepPlan &p, int C, bool direct, const float *u_t, const float *dphi,
+                               float dnu, float dax, float day, hipStream_t st) {
+    const int n = deep_fits(dt, p, C) ? deep_frame(dt, p, C) : 0;
+    if (n == 0 || dt.thermal || dt.bc_x == BC_NEE || dt.bc_y == BC_NEE) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(p.tiles_x * p.tiles_y));
+    const DeepPlan q{p.tiles_x, p.tiles_y, deep_stride(dt, p, C)};
+    const int dir = direct ? 1 : 0;
+#define MRT_TAND(CAP, NT) \
+    hipLaunchKernelGGL((k_tangent_deep<CAP, NT>), grid, dim3(NT), 0, st, dt, q, C, dir, u_t, dphi, dnu, dax, day)
+    if (n <= 512) MRT_TAND(512, 512);
+    else if (n <= 1024) MRT_TAND(1024, 1024);
+    else MRT_TAND(DEEP_CAP, 1024);
+#undef MRT_TAND
+    return hipGetLastError();
 }
 
 // Tangent of u at the state's time into du [2][ny][nx] (unpitched).

@@ -351,8 +351,9 @@ static bool deep_fits(const Dom &d, const DeepPlan &p, int C) {
 constexpr int DEEP_MOST_CYCLES = 10, DEEP_LEAST_CYCLES = 5;
 constexpr int DEEP_ONE_NODE = 1024, DEEP_ONE_NODE_CYCLES = 7;
 
-bool deep_plan(const Dom &d, DeepPlan *plan, int *cycles) {
+bool deep_plan(const Dom &d, int64_t most_tiles, DeepPlan *plan, int *cycles) {
     constexpr int CUS = 256;
+    if (most_tiles < 1) return false;
     const bool nee = d.bc_x == BC_NEE || d.bc_y == BC_NEE;
     if ((int64_t)d.nx * d.ny <= (nee ? 512 : (d.thermal ? 640 : 800))) {
         *plan = DeepPlan{1, 1, 0};
@@ -360,7 +361,7 @@ bool deep_plan(const Dom &d, DeepPlan *plan, int *cycles) {
         return true;
     }
     for (int rounds = 1; rounds <= (nee ? 5 : 1); ++rounds) {
-        const int wgs = CUS * rounds;
+        const int wgs = (int)std::min<int64_t>(CUS * rounds, most_tiles);
         int tx = (int)(std::sqrt((double)wgs * d.nx / d.ny) + 0.5);
         tx = std::min(std::max(tx, 1), std::min(d.nx, wgs));
         const int ty = std::min(wgs / tx, d.ny);

@@ -90,19 +90,22 @@ struct DeepPlan {
     int tiles_x, tiles_y;
     int stride;   // LDS row stride, set by the launch
 };
-// The plan of a domain that the deep pass serves and the most cycles per launch
-// (false: another pass is faster).
-bool deep_plan(const Dom &d, DeepPlan *plan, int *cycles);
+// The plan of a domain that the deep pass serves, on most_tiles tiles at most, and the
+// most cycles per launch (false: another pass is faster).
+bool deep_plan(const Dom &d, int64_t most_tiles, DeepPlan *plan, int *cycles);
 hipError_t launch_step_deep(const Dom &d, int storage, const DeepPlan &p, int cycles, bool direct, hipStream_t st);
 // the same recording u(t) of every cycle in d.urec, a record (five planes) per cycle
 hipError_t launch_step_deep_rec(const Dom &d, const DeepPlan &p, int cycles, bool direct, hipStream_t st);
 // The reverse pass on such tiles: `cycles` backward steps per launch, the records
 // of steps t, t - 1, ... at u_t, u_t - 5 planes, ...; acc: slots of the parameter
 // gradients, one per tile at most (NULL without them).
-bool adjoint_deep_plan(const Dom &d, int64_t slots, DeepPlan *plan, int *cycles);
 hipError_t launch_adjoint_deep(const Dom &d, const DeepPlan &p, int cycles, const float *lam_in, float *lam_out,
                                const float *lamg_in, float *lamg_out, const float *u_t, float *gphi, float *gkappa,
                                double *acc, hipStream_t st);
+// The tangent on such tiles: the records of steps t, t + 1, ... at u_t, u_t + 5
+// planes, ...; dt: the tangent's domain; direct: at t = 0.
+hipError_t launch_tangent_deep(const Dom &dt, const DeepPlan &p, int cycles, bool direct, const float *u_t,
+                               const float *dphi, float dnu, float dax, float day, hipStream_t st);
 
 // The strip pass (lbm_strip.h): the domain in `strips` column strips and `chunks`
 // runs of rows, one wavefront each.

@@ -1,6 +1,6 @@
 """Deep passes of the recorded run and of its reverse mode (the default on small domains)
 against one step per launch: the medium gradients bit for bit, the parameter gradients to
-the rounding of their sums. Both boundary kinds and periodic axes, with and without the
+the rounding of their sums, the tangent bit for bit. Both boundary kinds and periodic axes, with and without the
 thermal model, whole domains in one workgroup and tiled ones, frames of both sizes and
 segments of every length, over two calls."""
 import numpy as np
@@ -51,7 +51,9 @@ CASES = {
     "channel_401x350": (lambda: _channel(401, 350), 11, False),
     "heat_20x30": (lambda: _heat(20, 30), 40, False),
     "heat_111x90": (lambda: _heat(111, 90), 23, False),
+    "channel_520x500": (lambda: _channel(520, 500), 23, False),
     "heat_330x301": (lambda: _heat(330, 301), 13, False),
+    "heat_450x417": (lambda: _heat(450, 417), 13, False),
 }
 
 
@@ -85,3 +87,25 @@ def test_deep_gradients_are_those_of_single_steps(name):
     # both add the same FP32 shares of a node and step in FP64, in another order: at most
     # 7e6 shares, 2^-53 of their moduli each, for a sum 1e2 times smaller than their moduli
     np.testing.assert_allclose(t1, t0, rtol=1e-7)
+
+
+@pytest.mark.parametrize("name", [n for n in CASES if not n.startswith("heat")])
+def test_deep_tangent_is_that_of_single_steps(name):
+    make, every, kappa_plane = CASES[name]
+    case = make()
+    kap = None
+    if kappa_plane:
+        kap = torch.from_numpy((150.0 * (1 - case.phi) ** 2 / (case.phi ** 3 * case.dp ** 2)).astype(np.float32)).cuda()
+    out = []
+    for single in (True, False):
+        desc = lbm.desc_from_case(case, ckpt_every=every)
+        if kappa_plane:
+            desc.medium = lbm.MEDIUM_PHI_KAPPA
+        s = lbm.Solver(desc, phi=torch.from_numpy(case.phi).cuda(), kappa=kap, max_steps_recorded=60)
+        if single:
+            s.set_time_blocking(1)
+        s.step(49)
+        w = torch.cos(torch.arange(case.nx * case.ny, device="cuda", dtype=torch.float32)).reshape(case.ny, case.nx)
+        out.append(s.tangent(w, (0.3 * case.nu, 0.1, 0.2, 0.05)))
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1])
