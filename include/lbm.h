@@ -330,11 +330,12 @@ int lbm_set_time_blocking(lbm_ctx *c, int32_t cycles_per_pass);
 /* Small single domains (up to about 300,000 nodes isothermal, 200,000 with
  * the thermal model, about a million with on-node walls) step by deep passes
  * of up to ten cycles per launch, and domains of a few hundred nodes by up to
- * 1024; large ones (isothermal, no 1/K or viscosity plane, from 2^22 nodes)
- * by strip passes of six and four cycles. The mode reported below fills in
- * where they do not fit. A mode set here (and for the small ones a tile set by
- * lbm_set_two_cycle_tile or, with on-node walls, a launch shape) replaces
- * them. Deep passes run an adjoint's recomputation and
+ * 1024; mid-size ones (up to about five million nodes) by rolling passes of
+ * six, with the thermal model four cycles; large ones (isothermal, no 1/K or
+ * viscosity plane) by strip passes of six and four. The mode reported below
+ * fills in where these do not fit. A mode set here (and for the small and the
+ * mid-size ones a tile set by lbm_set_two_cycle_tile, or with on-node walls a
+ * launch shape) replaces them. Deep passes run an adjoint's recomputation and
  * its backward sweep too, and the tangent. Same bits as every other pass. */
 
 /* Current cycles per pass, and the workgroup size, tile rows (tiles are 64
@@ -356,7 +357,8 @@ int lbm_set_two_cycle_tile(lbm_ctx *c, int32_t threads, int32_t rows);
 
 /* Number of steps lbm_step replays from one hand-built HIP graph of kernel
  * nodes (up to 4096, rounded down to a whole number of passes; 0 launches
- * every step separately). Deep and strip passes are launched directly.
+ * every step separately). Deep, rolling and strip passes are launched
+ * directly.
  * Defaults: 0 for single domains, 32 for batches. Graphs are not used while
  * a trajectory is recorded for lbm_backward. Results do not depend on it. */
 int lbm_set_graph_steps(lbm_ctx *c, int32_t steps);

@@ -282,8 +282,9 @@ struct lbm_ctx {
     // pass or a tile
     DeepPlan deep{1, 1};
     int deep_cycles = 0;
-    // a large single domain in its default mode: strip passes (lbm_strip.h)
-    bool strip = false;
+    // in its default mode, a mid-size single domain: rolling passes (lbm_roll.h), a
+    // large one: strip passes (lbm_strip.h)
+    bool roll = false, strip = false;
 };
 
 namespace {
@@ -668,7 +669,9 @@ int lbm_create(const lbm_desc *d, const float *phi, const float *kappa, void *wo
     if (d->storage == LBM_FP16_DEV) c->sched = Schedule{64, 2, 2, 1};
     if (buffer_below_4gib(L)) {
         (void)deep_plan(D.dom, INT64_MAX, &c->deep, &c->deep_cycles);
-        c->strip = strip_domain(D.dom, d->storage == LBM_FP16_DEV ? ST_F16 : ST_F32);
+        const int st = d->storage == LBM_FP16_DEV ? ST_F16 : ST_F32;
+        c->roll = c->deep_cycles == 0 && roll_domain(D.dom, st);
+        c->strip = !c->roll && strip_domain(D.dom, st);
     }
     hipError_t e = init_domain(D, 0, phi, kappa, c->stream);
     if (e != hipSuccess) {
@@ -731,7 +734,7 @@ int lbm_step(lbm_ctx *c, int64_t n) {
         const int64_t next_ck = recording ? (c->t / c->dom[0].desc.ckpt_every + 1) * c->dom[0].desc.ckpt_every
                                           : INT64_MAX;
         const int64_t gcyc = graph_cycles(c);
-        if (gcyc > 0 && !recording && !c->strip && n - 1 >= gcyc) {
+        if (gcyc > 0 && !recording && !c->roll && !c->strip && n - 1 >= gcyc) {
             if (!c->gexec[c->cur]) {
                 if ((e = build_graph(c, c->cur)) != hipSuccess) return device_fail(c, e, "graph build");
             }
@@ -746,14 +749,18 @@ int lbm_step(lbm_ctx *c, int64_t n) {
         Domain &D = c->dom[0];
         const int st = D.desc.storage == LBM_FP16_DEV ? ST_F16 : ST_F32;
         int cycles = 1;
-        if (c->strip) cycles = strip_cycles(std::min(n, next_ck - c->t));
+        const int rolled = c->roll ? roll_cycles(D.dom, std::min(n, next_ck - c->t)) : 0;
+        if (rolled >= 3) cycles = rolled;
+        else if (c->strip) cycles = strip_cycles(std::min(n, next_ck - c->t));
         else if (fused && c->tblock == 4 && n >= 4 && c->t + 4 <= next_ck) cycles = 4;
         else if (fused && c->tblock >= 3 && n >= 3 && c->t + 3 <= next_ck) cycles = 3;
         else if (fused && n >= 2 && c->t + 2 <= next_ck) cycles = 2;
         const bool last = (n == cycles);
         const Dom d = last ? dom_rec(D, c->cur) : dom_for(D, c->cur);
         Dom *doms = last ? c->d_doms_rec : c->d_doms;
-        if (c->strip && cycles >= 4) {
+        if (rolled >= 3) {
+            e = launch_step_roll(d, st, cycles, c->stream);
+        } else if (c->strip && cycles >= 4) {
             e = launch_step_strip(d, st, cycles, c->stream);
         } else if (cycles == 4) {
             if (c->batch)
@@ -1159,7 +1166,7 @@ int lbm_set_time_blocking(lbm_ctx *c, int32_t cycles_per_pass) {
     }
     c->tblock = cycles_per_pass;
     c->deep_cycles = 0;
-    c->strip = false;
+    c->roll = c->strip = false;
     reset_graphs(c);
     return LBM_OK;
 }
@@ -1173,6 +1180,7 @@ int lbm_set_two_cycle_tile(lbm_ctx *c, int32_t threads, int32_t rows) {
     c->tb_threads = threads;
     c->tb_rows = rows;
     c->deep_cycles = 0;
+    c->roll = false;
     reset_graphs(c);
     return LBM_OK;
 }

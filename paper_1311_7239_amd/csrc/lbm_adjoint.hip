@@ -16,6 +16,7 @@
 
 #include "lbm_deep.h"
 #include "lbm_launch.h"
+#include "lbm_roll.h"
 #include "lbm_strip.h"
 
 namespace mrt {

@@ -107,6 +107,16 @@ hipError_t launch_adjoint_deep(const Dom &d, const DeepPlan &p, int cycles, cons
 hipError_t launch_tangent_deep(const Dom &dt, const DeepPlan &p, int cycles, bool direct, const float *u_t,
                                const float *dphi, float dnu, float dax, float day, hipStream_t st);
 
+// The rolling pass (lbm_roll.h): strips of 64 columns, runs of rows each.
+struct RollPlan {
+    int strips, runs;
+};
+// Whether a domain takes them, and the cycles of the next pass with n left (0: another
+// pass).
+bool roll_domain(const Dom &d, int storage);
+int roll_cycles(const Dom &d, int64_t n);
+hipError_t launch_step_roll(const Dom &d, int storage, int cycles, hipStream_t st);
+
 // The strip pass (lbm_strip.h): the domain in `strips` column strips and `chunks`
 // runs of rows, one wavefront each.
 struct StripPlan {

@@ -459,8 +459,8 @@ static const void *strip_fn_c(const Dom &d) {
     }
 }
 
-// Where the strip pass is taken (us per step in 48-step calls, the tile passes'
-// default against the strip pass, one box): log-normal channels in FP32 from 2^22
+// Where the strip pass is taken, unless the rolling pass (lbm_roll.h) is (us per step
+// in 48-step calls, the tile passes' default against the strip pass, one box): log-normal channels in FP32 from 2^22
 // nodes (2048^2 23.5 against 20.1, 3000^2 46.8 against 37.9, 4096^2 81 against 65,
 // 8192^2 294 against 224; 1750^2 15.2 against 15.7); binary16 storage, whose tile
 // passes move half the bytes, from 6 x 2^20 (channel 2500^2 28.4 against 26.9,

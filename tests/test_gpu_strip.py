@@ -39,6 +39,11 @@ CASES = [
     (P, W, 3001, 2101, True, lbm.FP16_DEV),     # odd pairs in binary16
     (P, W, 2900, 2935, False, lbm.FP16_DEV),
     (W, P, 2600, 2431, False, lbm.FP16_DEV),
+    # above the sizes that rolling passes take
+    (P, W, 2731, 2049, True, lbm.FP32_DEV),
+    (P, P, 1161, 5001, True, lbm.FP32_DEV),
+    (W, P, 16385, 401, True, lbm.FP32_DEV),
+    (W, W, 2047, 2700, True, lbm.FP32_DEV),
 ]
 
 
