@@ -236,6 +236,15 @@ struct Domain {
 
 }  // namespace
 
+namespace {
+// A batch's table of runs, one group of domains after another: group g has the
+// entries from first[g] on.
+struct BatchRuns {
+    std::vector<int4> items;
+    std::vector<int> first;
+};
+}  // namespace
+
 struct lbm_ctx {
     std::vector<Domain> dom;
     hipStream_t stream = nullptr;
@@ -267,6 +276,10 @@ struct lbm_ctx {
     bool four_ok = false;       // an isothermal batch with bounce-back walls: four cycles available
     std::vector<int4> h_tiles4;
     std::vector<int4> h_tiles2;
+    // runs of the batched rolling pass, one table per number of cycles (kRollCycles)
+    int4 *d_runs[3] = {nullptr, nullptr, nullptr};
+    BatchRuns h_runs[3];
+    bool runs_nt = false;       // a group of them is larger than the cache
     // steps replayed from one hand-built HIP graph (0: launch each step);
     // one executable graph per starting buffer parity
     int graph_steps = 0;
@@ -282,8 +295,8 @@ struct lbm_ctx {
     // pass or a tile
     DeepPlan deep{1, 1};
     int deep_cycles = 0;
-    // in its default mode, a mid-size single domain: rolling passes (lbm_roll.h), a
-    // large one: strip passes (lbm_strip.h)
+    // in its default mode, a mid-size single domain or a batch: rolling passes
+    // (lbm_roll.h), a large single domain: strip passes (lbm_strip.h)
     bool roll = false, strip = false;
 };
 
@@ -468,6 +481,10 @@ int64_t deep_pass_cycles(const lbm_ctx *c, int64_t n) {
     if (c->rec_valid && every > 0) n = std::min<int64_t>(n, every - c->t % every);
     return deep_run_cycles(c, n);
 }
+
+// Cycles of the batched rolling passes, a table of runs for each.
+const int kRollCycles[3] = {3, 4, 6};
+int roll_table(int cycles) { return cycles == 6 ? 2 : cycles - 3; }
 
 // cycles advanced by one kernel node of the step graph
 int graph_node_steps(const lbm_ctx *c) { return c->tblock; }
@@ -749,7 +766,30 @@ int lbm_step(lbm_ctx *c, int64_t n) {
         Domain &D = c->dom[0];
         const int st = D.desc.storage == LBM_FP16_DEV ? ST_F16 : ST_F32;
         int cycles = 1;
-        const int rolled = c->roll ? roll_cycles(D.dom, std::min(n, next_ck - c->t)) : 0;
+        const bool any_medium = c->batch ? !c->batch_uniform : medium_kind(D.dom) == MK_ANY;
+        const int rolled = c->roll ? roll_cycles(D.dom.thermal != 0, any_medium, std::min(n, next_ck - c->t)) : 0;
+        if (c->batch && rolled >= 3) {
+            // one group of domains after another through all its rolling passes
+            int64_t left = n;
+            int cur = c->cur;
+            for (size_t g = 0; g + 1 < c->h_runs[0].first.size(); ++g) {
+                left = n;
+                cur = c->cur;
+                for (int k; (k = roll_cycles(c->batch_thermal, any_medium, left)) >= 3; cur ^= 1) {
+                    left -= k;
+                    const BatchRuns &runs = c->h_runs[roll_table(k)];
+                    e = launch_step_roll_batch(left == 0 ? c->d_doms_rec : c->d_doms,
+                                               c->d_runs[roll_table(k)] + runs.first[g], runs.first[g + 1] - runs.first[g],
+                                               k, cur, c->runs_nt ? 1 : 0, c->storage, c->batch_thermal,
+                                               c->batch_uniform, c->stream);
+                    if (e != hipSuccess) return device_fail(c, e, "step launch");
+                }
+            }
+            c->cur = cur;
+            c->t += n - left;
+            n = left;
+            continue;
+        }
         if (rolled >= 3) cycles = rolled;
         else if (c->strip) cycles = strip_cycles(std::min(n, next_ck - c->t));
         else if (fused && c->tblock == 4 && n >= 4 && c->t + 4 <= next_ck) cycles = 4;
@@ -1256,7 +1296,7 @@ int64_t batch_tiles(int32_t n, const lbm_desc *descs, const Schedule &s) {
 
 struct BatchLayout {
     std::vector<size_t> off;  // per-domain base offsets
-    size_t off_doms = 0, off_tiles = 0, off_tiles2 = 0, off_tiles4 = 0, total = 0;
+    size_t off_doms = 0, off_tiles = 0, off_tiles2 = 0, off_tiles4 = 0, off_runs[3] = {0, 0, 0}, total = 0;
     int64_t max_tiles = 0, max_tiles2 = 0, tiles4 = 0;
 };
 
@@ -1270,6 +1310,91 @@ int64_t batch_tiles2(int32_t n, const lbm_desc *descs, int rows) {
         total += (int64_t)tx * ty;
     }
     return total;
+}
+
+bool batch_is_uniform(int32_t n, const lbm_desc *descs) {
+    for (int32_t k = 0; k < n; ++k)
+        if (descs[k].medium != LBM_MEDIUM_UNIFORM || descs[k].j_plane) return false;
+    return true;
+}
+
+// Both state buffers of a domain
+size_t state_bytes_of(const lbm_desc &d) {
+    const Layout L = make_layout(d, 0);
+    return 2 * (L.f_bytes + L.g_bytes);
+}
+
+// The groups of domains (group g from first[g] on) that a batch steps in rolling passes,
+// one group after another through all the passes of a call: nearly equal shares of it
+// that the 256 MB Infinity Cache serves. us per step of the whole batch, in groups of at
+// most 128 / 232 / 448 MB and in one: 60 heated cavities of 300 to 768 nodes a side 137
+// / 120 / 155 / 186 (in tiles 197); 16 cavities of 1000^2, whose re-read state the cache
+// serves in part, 89 / 72 / 64 / 70 (tiles 70). Binary16 flow is not bound by memory:
+// 60 cavities 62 / 53 / 54 / 45 (tiles 54).
+std::vector<int32_t> batch_groups(int32_t n, const lbm_desc *descs, size_t *largest) {
+    const bool thermal = descs[0].thermal.enabled != 0;
+    const size_t most = thermal ? (size_t)232 << 20
+                                : (descs[0].storage == LBM_FP16_DEV ? SIZE_MAX : (size_t)448 << 20);
+    size_t all = 0, sum = 0;
+    for (int32_t k = 0; k < n; ++k) all += state_bytes_of(descs[k]);
+    const size_t groups = all / most + 1, share = all / groups + 1;
+    std::vector<int32_t> first{0};
+    *largest = 0;
+    for (int32_t k = 0; k < n; ++k) {
+        const size_t b = state_bytes_of(descs[k]);
+        // a domain that lies in this share by more than half still belongs to it
+        if (sum > 0 && sum + b / 2 > share) {
+            first.push_back(k);
+            sum = 0;
+        }
+        sum += b;
+        *largest = std::max(*largest, sum);
+    }
+    first.push_back(n);
+    return first;
+}
+
+// Whether a batch steps in rolling passes (us per step, the autotuned tiles against
+// them, one box): 60 cavities of 48 to 300 nodes a side 16.3 against 12.7, in binary16
+// 15.1 against 13.4; 60 of 64 to 768 in FP32 54.6 against 51.6, with porosity planes
+// 60.2 against 58.4; the 27 heated cavities of Table 1 16.0 against 9.4; 2000 cavities
+// of 16 to 60 nodes 27.7 against 23.5. Not where a domain is of the sizes that single
+// domains do not roll either (two of 3000 to 4000 nodes a side 88.6 against 108), nor in
+// FP32 in uniform media with domains beyond 1100^2 in more than one group (20 of 1500^2
+// 178 against 186; three of 2240^2 59.3 against 60.8, but 16 of 1000^2 69.5 against
+// 63.9), whose tiles load no porosity.
+bool roll_batch(int32_t n, const lbm_desc *descs) {
+    const int64_t M = (int64_t)1 << 20;
+    int64_t largest = 0;
+    size_t all = 0;
+    for (int32_t k = 0; k < n; ++k) {
+        const lbm_desc &d = descs[k];
+        if (!roll_batch_domain(RollShape{d.nx, d.ny, d.bc_x == LBM_PERIODIC}, d.bc_y == LBM_PERIODIC) || on_node_walls(d))
+            return false;
+        largest = std::max(largest, (int64_t)d.nx * d.ny);
+        all += state_bytes_of(d);
+    }
+    if (descs[0].thermal.enabled) return largest <= 9 * M / 2;
+    if (descs[0].storage == LBM_FP32_DEV && batch_is_uniform(n, descs) && all > ((size_t)448 << 20))
+        return largest <= 5 * M / 4;
+    return largest <= 5 * M;
+}
+
+BatchRuns batch_runs(int32_t n, const lbm_desc *descs, int cycles) {
+    BatchRuns B;
+    if (!roll_batch(n, descs)) return B;
+    size_t largest;
+    const std::vector<int32_t> first = batch_groups(n, descs, &largest);
+    for (size_t g = 0; g + 1 < first.size(); ++g) {
+        std::vector<RollShape> shapes;
+        for (int32_t k = first[g]; k < first[g + 1]; ++k)
+            shapes.push_back(RollShape{descs[k].nx, descs[k].ny, descs[k].bc_x == LBM_PERIODIC});
+        const std::vector<int4> items = roll_batch_items(shapes, first[g], cycles);
+        B.first.push_back((int)B.items.size());
+        B.items.insert(B.items.end(), items.begin(), items.end());
+    }
+    B.first.push_back((int)B.items.size());
+    return B;
 }
 
 BatchLayout batch_layout(int32_t n, const lbm_desc *descs) {
@@ -1296,6 +1421,10 @@ BatchLayout batch_layout(int32_t n, const lbm_desc *descs) {
     B.tiles4 = batch_tiles2(n, descs, step4_rows());
     B.off_tiles4 = o;
     o = align_up(o + sizeof(int4) * (size_t)B.tiles4, ALIGN);
+    for (int q = 0; q < 3; ++q) {
+        B.off_runs[q] = o;
+        o = align_up(o + sizeof(int4) * batch_runs(n, descs, kRollCycles[q]).items.size(), ALIGN);
+    }
     B.total = o;
     return B;
 }
@@ -1594,6 +1723,19 @@ extern "C" int lbm_create_batch(int32_t n, const lbm_desc *descs, const float *c
     if (e == hipSuccess && !c->batch_thermal && two_cycle_possible(c)) {
         e = upload_tiles4(c);
         c->four_ok = e == hipSuccess;
+    }
+    if (e == hipSuccess && roll_batch(n, descs)) {
+        for (int q = 0; q < 3 && e == hipSuccess; ++q) {
+            c->d_runs[q] = (int4 *)(base + B.off_runs[q]);
+            c->h_runs[q] = batch_runs(n, descs, kRollCycles[q]);
+            e = hipMemcpyAsync(c->d_runs[q], c->h_runs[q].items.data(), sizeof(int4) * c->h_runs[q].items.size(),
+                               hipMemcpyHostToDevice, c->stream);
+        }
+        size_t largest;
+        (void)batch_groups(n, descs, &largest);
+        c->runs_nt = largest / 2 >= kCacheBytes;
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        c->roll = e == hipSuccess;
     }
     // a tuning-cache entry cannot select a mode this batch does not have
     if (c->batch_thermal && c->tblock > 2) c->tblock = 2;

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "lbm_device.h"
 
 namespace mrt {
@@ -114,8 +116,19 @@ struct RollPlan {
 // Whether a domain takes them, and the cycles of the next pass with n left (0: another
 // pass).
 bool roll_domain(const Dom &d, int storage);
-int roll_cycles(const Dom &d, int64_t n);
+int roll_cycles(bool thermal, bool any_medium, int64_t n);
 hipError_t launch_step_roll(const Dom &d, int storage, int cycles, hipStream_t st);
+// The same over a group of a batch's domains, `first` being its first: the table of its
+// runs for passes of `cycles` cycles (3, 4 or 6), one workgroup each, and whether a
+// domain admits them.
+struct RollShape {
+    int nx, ny;
+    bool per_x;
+};
+std::vector<int4> roll_batch_items(const std::vector<RollShape> &doms, int first, int cycles);
+bool roll_batch_domain(const RollShape &s, bool per_y);
+hipError_t launch_step_roll_batch(const Dom *doms, const int4 *items, int nitems, int cycles, int parity, int nt_store,
+                                  int storage, bool thermal, bool uniform, hipStream_t st);
 
 // The strip pass (lbm_strip.h): the domain in `strips` column strips and `chunks`
 // runs of rows, one wavefront each.

@@ -27,6 +27,7 @@
 
 #include <algorithm>
 #include <type_traits>
+#include <vector>
 
 #include "lbm_launch.h"
 #include "lbm_strip.h"
@@ -53,9 +54,9 @@ __host__ __device__ inline int roll_begin(int k, int nx, bool periodic, int C) {
     return g + (int)((int64_t)k * (nx - 2 * g) / n);
 }
 
+// Strip sk of p.strips and run rk of p.runs of a domain.
 template <typename S, int C, int MK, bool THERMAL>
-__global__ __launch_bounds__(64 * ROLL_ROWS) __attribute__((amdgpu_waves_per_eu(4))) void k_step3_roll(
-    Dom d, RollPlan p) {
+__device__ __forceinline__ void roll_run(const Dom &d, const RollPlan &p, int sk, int rk) {
     static_assert(C >= 3, "a barrier between a cycle's reads and the next rows' writes");
     constexpr int H = ROLL_ROWS, RING = H + 2, G = C - 1, ES = (int)sizeof(S);
     constexpr bool CELLS = MK != MK_UNIFORM, SNU = MK == MK_ANY;
@@ -72,9 +73,7 @@ __global__ __launch_bounds__(64 * ROLL_ROWS) __attribute__((amdgpu_waves_per_eu(
     __shared__ float4 cells[CELLS ? CR * 64 : 1];
     __shared__ float snus[SNU ? CR * 64 : 1];
     const int lane = (int)threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int item = xcd_swizzle((int)blockIdx.x, (int)gridDim.x);
     const bool per_x = d.bc_x == BC_PERIODIC, per_y = d.bc_y == BC_PERIODIC;
-    const int sk = item % p.strips, rk = item / p.strips;
     const int c0 = roll_begin(sk, d.nx, per_x, C), c1 = roll_begin(sk + 1, d.nx, per_x, C);
     const int y0 = (int)((int64_t)rk * d.ny / p.runs), y1 = (int)((int64_t)(rk + 1) * d.ny / p.runs);
     const int xa = (per_x ? c0 - G : std::max(c0 - G, 0)) + lane;
@@ -308,6 +307,28 @@ __global__ __launch_bounds__(64 * ROLL_ROWS) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
+template <typename S, int C, int MK, bool THERMAL>
+__global__ __launch_bounds__(64 * ROLL_ROWS) __attribute__((amdgpu_waves_per_eu(4))) void k_step3_roll(
+    Dom d, RollPlan p) {
+    const int item = xcd_swizzle((int)blockIdx.x, (int)gridDim.x);
+    roll_run<S, C, MK, THERMAL>(d, p, item % p.strips, item / p.strips);
+}
+
+// The same over a table of runs (domain, strip, run, runs of the domain; domain -1: none),
+// for the domains of a batch: every run of all of them in one launch, against tiles of
+// four cycles (two with the D2Q5 field) whose rings cost a small domain the most. 60
+// cavities of 64 to 768 nodes a side 70 -> 62 us per step, the 27 heated cavities of
+// Table 1 16.0 -> 9.4, 60 heated ones of 64 to 400 51 -> 27.
+template <typename S, int C, int MK, bool THERMAL>
+__global__ __launch_bounds__(64 * ROLL_ROWS) __attribute__((amdgpu_waves_per_eu(4))) void k_step3_roll_batch(
+    const Dom *__restrict__ doms, const int4 *__restrict__ items, int parity, int nt_store) {
+    const int4 it = items[blockIdx.x];
+    if (it.x < 0) return;
+    Dom d = doms[2 * it.x + parity];
+    d.nt_store = nt_store;
+    roll_run<S, C, MK, THERMAL>(d, RollPlan{roll_strips(d.nx, d.bc_x == BC_PERIODIC, C), it.w}, it.y, it.z);
+}
+
 // Two workgroups per CU (LDS: at most 80 KB each) in one round.
 static RollPlan roll_plan(const Dom &d, int C) {
     RollPlan p{roll_strips(d.nx, d.bc_x == BC_PERIODIC, C), 0};
@@ -338,11 +359,12 @@ static const void *roll_fn_mk(const Dom &d, int cycles) {
 }
 
 // Cycles of the next rolling pass with n left (0: another pass): six, or with the
-// D2Q5 field four, and fours and threes where they come out even.
-int roll_cycles(const Dom &d, int64_t n) {
+// D2Q5 field four (three in a medium of any kind), and fours and threes where they
+// come out even.
+int roll_cycles(bool thermal, bool any_medium, int64_t n) {
     if (n < 3) return 0;
-    if (!d.thermal) return strip_cycles(n);
-    if (medium_kind(d) == MK_ANY) return 3;
+    if (!thermal) return strip_cycles(n);
+    if (any_medium) return 3;
     return n == 3 || n == 6 || n == 9 ? 3 : (n == 5 ? 3 : 4);
 }
 
@@ -375,6 +397,105 @@ hipError_t launch_step_roll(const Dom &d, int storage, int cycles, hipStream_t s
     RollPlan p = roll_plan(d, cycles);
     void *args[2] = {&dd, &p};
     return hipLaunchKernel(fn, dim3((unsigned)(p.strips * p.runs)), dim3(64 * ROLL_ROWS), args, 0, st);
+}
+
+// ---- batches
+
+template <typename S, bool THERMAL, int MK>
+static const void *roll_batch_fn_t(int cycles) {
+    if (cycles == 3) return (const void *)&k_step3_roll_batch<S, 3, MK, THERMAL>;
+    if constexpr (!THERMAL || MK != MK_ANY)
+        if (cycles == 4) return (const void *)&k_step3_roll_batch<S, 4, MK, THERMAL>;
+    if constexpr (!THERMAL)
+        if (cycles == 6) return (const void *)&k_step3_roll_batch<S, 6, MK, THERMAL>;
+    return nullptr;
+}
+
+template <typename S>
+static const void *roll_batch_fn(int cycles, bool thermal, bool uniform) {
+    if (thermal)
+        return uniform ? roll_batch_fn_t<S, true, MK_UNIFORM>(cycles) : roll_batch_fn_t<S, true, MK_ANY>(cycles);
+    return uniform ? roll_batch_fn_t<S, false, MK_UNIFORM>(cycles) : roll_batch_fn_t<S, false, MK_ANY>(cycles);
+}
+
+// Turns of eight rows that a run of `rows` rows takes, and one for its first load.
+static int64_t roll_turns(int rows, int C) { return (rows + 2 * (C - 1) + ROLL_ROWS - 1) / ROLL_ROWS + 1; }
+
+// The runs of a batch in the order of their launch. At most R rows each, for the R
+// that ends first: no sooner than the longest run, nor (in more than one round of
+// workgroups, two per CU) than the turns of all together and a tenth of the longest.
+// The longest run goes first, and eight strips side by side go to one XCD (which
+// workgroup b % 8 tells), so that every XCD has its share of long ones (12 cavities of
+// 160 to 760 nodes 17.9 us per step in the order of the domains, 16.6 so; the 27 heated
+// cavities of Table 1 10.0, 9.4).
+std::vector<int4> roll_batch_items(const std::vector<RollShape> &doms, int first, int C) {
+    constexpr int64_t SLOTS = 512;
+    int tallest = 1;
+    for (const RollShape &s : doms) tallest = std::max(tallest, s.ny);
+    auto count = [&](int R) -> int64_t {
+        int64_t n = 0;
+        for (const RollShape &s : doms) n += (int64_t)roll_strips(s.nx, s.per_x, C) * ((s.ny + R - 1) / R);
+        return n;
+    };
+    int best_rows = tallest;
+    double best = 1e300;
+    for (int rounds = 1; rounds <= 8; ++rounds) {
+        int lo = 1, hi = tallest;   // the fewest rows that need no more rounds
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (count(mid) <= SLOTS * rounds) hi = mid;
+            else lo = mid + 1;
+        }
+        int64_t all = 0, longest = 0;
+        for (const RollShape &s : doms) {
+            const int runs = (s.ny + lo - 1) / lo;
+            const int64_t t = roll_turns((s.ny + runs - 1) / runs, C);
+            all += t * runs * roll_strips(s.nx, s.per_x, C);
+            longest = std::max(longest, t);
+        }
+        const double one = (double)longest, many = (double)all / SLOTS + 0.1 * (double)longest;
+        const double cost = count(lo) <= SLOTS ? one : std::max(one, many);
+        if (cost < best) {
+            best = cost;
+            best_rows = lo;
+        }
+    }
+    struct Run {
+        int domain, run, runs, rows;
+    };
+    std::vector<Run> order;
+    for (size_t k = 0; k < doms.size(); ++k) {
+        const int64_t runs = (doms[k].ny + best_rows - 1) / best_rows;
+        for (int64_t r = 0; r < runs; ++r)
+            order.push_back(Run{(int)k, (int)r, (int)runs, (int)((r + 1) * doms[k].ny / runs - r * doms[k].ny / runs)});
+    }
+    std::stable_sort(order.begin(), order.end(), [](const Run &a, const Run &b) { return a.rows > b.rows; });
+    std::vector<int4> list;
+    for (const Run &q : order)
+        for (int s = 0; s < roll_strips(doms[(size_t)q.domain].nx, doms[(size_t)q.domain].per_x, C); ++s)
+            list.push_back(make_int4(first + q.domain, s, q.run, q.runs));
+    constexpr size_t XCDS = 8, SIDE = 8;
+    std::vector<int4> items((list.size() + XCDS * SIDE - 1) / (XCDS * SIDE) * (XCDS * SIDE), make_int4(-1, 0, 0, 0));
+    for (size_t j = 0; j < list.size(); ++j) {
+        const size_t chunk = j / SIDE;
+        items[((chunk / XCDS) * SIDE + j % SIDE) * XCDS + chunk % XCDS] = list[j];
+    }
+    return items;
+}
+
+// What the rolling pass can run in a batch (bounce-back walls): the ring wraps around a
+// periodic axis once.
+bool roll_batch_domain(const RollShape &s, bool per_y) {
+    return s.nx >= (s.per_x ? ROLL_COLS : 16) && s.ny >= (per_y ? ROLL_COLS : 16);
+}
+
+hipError_t launch_step_roll_batch(const Dom *doms, const int4 *items, int nitems, int cycles, int parity, int nt_store,
+                                  int storage, bool thermal, bool uniform, hipStream_t st) {
+    const void *fn = storage == ST_F32 ? roll_batch_fn<float>(cycles, thermal, uniform)
+                                       : roll_batch_fn<_Float16>(cycles, thermal, uniform);
+    if (!fn || nitems < 1) return hipErrorInvalidValue;
+    void *args[4] = {&doms, &items, &parity, &nt_store};
+    return hipLaunchKernel(fn, dim3((unsigned)nitems), dim3(64 * ROLL_ROWS), args, 0, st);
 }
 
 }  // namespace mrt
