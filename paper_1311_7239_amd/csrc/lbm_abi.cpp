@@ -1771,9 +1771,14 @@ int backward_impl(lbm_ctx *c, const float *dL_du, float *dL_dphi, float *dL_dkap
     const bool th = d.thermal.enabled != 0;
     // The recomputation's passes record u at every cycle and give the same bits
     // whatever their length; from 2^22 nodes isothermal domains in mode 3 or 4 take
-    // four-cycle recording passes (2048^2: backward 256 ms against 274.5 with
-    // three-cycle ones).
+    // four-cycle recording passes in tiles (2048^2: backward 256 ms against 274.5 with
+    // three-cycle ones), where they do not roll.
     const bool rec4 = !th && (c->tblock == 4 || (c->tblock == 3 && (int64_t)d.nx * d.ny >= ((int64_t)1 << 22)));
+    // Rolling domains record in rolling passes, up to 2^22 nodes (us per step of a backward
+    // pass, segments of 60, against the tiles: log-normal channel 1024^2 20.3 -> 19.0, 1500^2
+    // 35.0 -> 33.0, 2048^2 64.7 -> 64.3; with a 1/K plane 2000^2 80 -> 73; heated 1500^2 62
+    // -> 57, 2000^2 128 -> 127; but 2200^2 in segments of 61 77.7 -> 80.0).
+    const bool roll_rec = c->roll && (int64_t)d.nx * d.ny <= ((int64_t)1 << 22);
     if (dL_dkappa && d.medium != LBM_MEDIUM_PHI_KAPPA) return fail(LBM_EINVAL, "dL_dkappa needs LBM_MEDIUM_PHI_KAPPA");
     if (!c->rec_valid) return fail(LBM_ESTATE, "no recorded trajectory leads to the current state");
     const int64_t T = c->t, k = d.ckpt_every;
@@ -1828,6 +1833,10 @@ int backward_impl(lbm_ctx *c, const float *dL_du, float *dL_dphi, float *dL_dkap
                 if (const int64_t deep = deep_run_cycles(c, s1 - t); deep > 0) {
                     e = launch_step_deep_rec(dr, c->deep, (int)deep, t == 0, st);
                     t += deep;
+                } else if (const int rolled = roll_rec && t > 0 ? roll_cycles(th, medium_kind(D.dom) != MK_ERGUN, s1 - t) : 0;
+                           rolled >= 3) {
+                    e = launch_step_roll_rec(dr, rolled, st);
+                    t += rolled;
                 } else if (rec4 && t > 0 && t + 3 < s1) {
                     // four cycles in one pass, recording at t, t + 1, t + 2 and t + 3
                     e = launch_step4_rec(dr, c->sched.swizzle, dr.urec + rstride, dr.urec + 2 * rstride,

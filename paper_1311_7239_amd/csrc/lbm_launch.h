@@ -118,6 +118,9 @@ struct RollPlan {
 bool roll_domain(const Dom &d, int storage);
 int roll_cycles(bool thermal, bool any_medium, int64_t n);
 hipError_t launch_step_roll(const Dom &d, int storage, int cycles, hipStream_t st);
+// the same recording u(t) of every cycle in d.urec, a record (five planes) per cycle;
+// any_medium for its cycles: not the closed-form Ergun medium
+hipError_t launch_step_roll_rec(const Dom &d, int cycles, hipStream_t st);
 // The same over a group of a batch's domains, `first` being its first: the table of its
 // runs for passes of `cycles` cycles (3, 4 or 6), one workgroup each, and whether a
 // domain admits them.

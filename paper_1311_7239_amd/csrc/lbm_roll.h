@@ -23,6 +23,9 @@
 // 2048^2 channel 22.6 -> 19.7. Two workgroups of eight wavefronts per CU are the best
 // shape: four cycles (LDS for four workgroups) 6.1 with two, 6.6 with four, 6.2 with
 // one of sixteen wavefronts.
+//
+// A batch runs the strips of all its domains from one table (k_step3_roll_batch), and
+// the adjoint's recomputation records in these passes too (REC).
 #pragma once
 
 #include <algorithm>
@@ -54,8 +57,10 @@ __host__ __device__ inline int roll_begin(int k, int nx, bool periodic, int C) {
     return g + (int)((int64_t)k * (nx - 2 * g) / n);
 }
 
-// Strip sk of p.strips and run rk of p.runs of a domain.
-template <typename S, int C, int MK, bool THERMAL>
+// Strip sk of p.strips and run rk of p.runs of a domain. REC: every cycle also records
+// its velocity for the adjoint (and the stress moments and the temperature), cycle k
+// five planes after cycle k - 1.
+template <typename S, int C, int MK, bool THERMAL, bool REC>
 __device__ __forceinline__ void roll_run(const Dom &d, const RollPlan &p, int sk, int rk) {
     static_assert(C >= 3, "a barrier between a cycle's reads and the next rows' writes");
     constexpr int H = ROLL_ROWS, RING = H + 2, G = C - 1, ES = (int)sizeof(S);
@@ -93,7 +98,7 @@ __device__ __forceinline__ void roll_run(const Dom &d, const RollPlan &p, int sk
     const BufRes rgout = buf_res(THERMAL ? d.gout : nullptr, THERMAL ? 5 * plg : 0u);
     const MediumSrc<MK> med(d);
     constexpr uint32_t NOWHERE = 0xfffffff0u;   // beyond the buffers: a store there is dropped
-    const uint32_t vst = in ? (uint32_t)(col * ES) : NOWHERE, vsg = in ? (uint32_t)(col * 4) : NOWHERE;
+    const uint32_t vst = in ? (uint32_t)(col * ES) : NOWHERE, vs4 = in ? (uint32_t)(col * 4) : NOWHERE;
 
     const int lo = per_y ? y0 - G : std::max(y0 - G, 0), hi = per_y ? y1 + G : std::min(y1 + G, d.ny);
     auto wrap_row = [&](int y) -> int {
@@ -205,6 +210,17 @@ __device__ __forceinline__ void roll_run(const Dom &d, const RollPlan &p, int sk
                 }
                 float ux, uy, n7, n8, dT;
                 node_update<THERMAL>(d, c, f, g, ux, uy, n7, n8, dT);
+                if (REC && y >= y0 && y < y1) {
+                    const BufRes rec = buf_res(d.urec + (int64_t)k * 5 * d.plane, 5 * plg);
+                    const uint32_t so = (uint32_t)y * rowg;
+                    BufIO<float>::st_nt(rec, vs4, so, ux);
+                    BufIO<float>::st_nt(rec, vs4, so + plg, uy);
+                    if (d.rec_stress) {
+                        BufIO<float>::st_nt(rec, vs4, so + 2 * plg, n7);
+                        BufIO<float>::st_nt(rec, vs4, so + 3 * plg, n8);
+                    }
+                    if (THERMAL) BufIO<float>::st_nt(rec, vs4, so + 4 * plg, dT);
+                }
                 if (k < C - 1) {
                     float *B = lds + k * LF, *Bg = ldsg + (THERMAL ? k * LG : 0);
 #pragma unroll
@@ -245,8 +261,8 @@ __device__ __forceinline__ void roll_run(const Dom &d, const RollPlan &p, int sk
                     if (THERMAL) {
 #pragma unroll
                         for (int j = 0; j < 5; ++j) {
-                            if (d.nt_store) BufIO<float>::st_nt(rgout, vsg, sg + (uint32_t)j * plg, g[j]);
-                            else BufIO<float>::st(rgout, vsg, sg + (uint32_t)j * plg, g[j]);
+                            if (d.nt_store) BufIO<float>::st_nt(rgout, vs4, sg + (uint32_t)j * plg, g[j]);
+                            else BufIO<float>::st(rgout, vs4, sg + (uint32_t)j * plg, g[j]);
                         }
                     }
                     if (d.uprev && in) store_uprev(d, sg + (uint32_t)(col * 4), ux, uy);
@@ -307,11 +323,11 @@ __device__ __forceinline__ void roll_run(const Dom &d, const RollPlan &p, int sk
     }
 }
 
-template <typename S, int C, int MK, bool THERMAL>
+template <typename S, int C, int MK, bool THERMAL, bool REC>
 __global__ __launch_bounds__(64 * ROLL_ROWS) __attribute__((amdgpu_waves_per_eu(4))) void k_step3_roll(
     Dom d, RollPlan p) {
     const int item = xcd_swizzle((int)blockIdx.x, (int)gridDim.x);
-    roll_run<S, C, MK, THERMAL>(d, p, item % p.strips, item / p.strips);
+    roll_run<S, C, MK, THERMAL, REC>(d, p, item % p.strips, item / p.strips);
 }
 
 // The same over a table of runs (domain, strip, run, runs of the domain; domain -1: none),
@@ -326,7 +342,7 @@ __global__ __launch_bounds__(64 * ROLL_ROWS) __attribute__((amdgpu_waves_per_eu(
     if (it.x < 0) return;
     Dom d = doms[2 * it.x + parity];
     d.nt_store = nt_store;
-    roll_run<S, C, MK, THERMAL>(d, RollPlan{roll_strips(d.nx, d.bc_x == BC_PERIODIC, C), it.w}, it.y, it.z);
+    roll_run<S, C, MK, THERMAL, false>(d, RollPlan{roll_strips(d.nx, d.bc_x == BC_PERIODIC, C), it.w}, it.y, it.z);
 }
 
 // Two workgroups per CU (LDS: at most 80 KB each) in one round.
@@ -339,22 +355,22 @@ static RollPlan roll_plan(const Dom &d, int C) {
 // The kernel of a pass (NULL: none compiled), the most cycles that two workgroups'
 // LDS holds being six, with the D2Q5 field four, and three beside the cells of
 // MK_ANY.
-template <typename S, bool THERMAL, int MK>
+template <typename S, bool THERMAL, bool REC, int MK>
 static const void *roll_fn_t(int cycles) {
-    if (cycles == 3) return (const void *)&k_step3_roll<S, 3, MK, THERMAL>;
+    if (cycles == 3) return (const void *)&k_step3_roll<S, 3, MK, THERMAL, REC>;
     if constexpr (!THERMAL || MK != MK_ANY)
-        if (cycles == 4) return (const void *)&k_step3_roll<S, 4, MK, THERMAL>;
+        if (cycles == 4) return (const void *)&k_step3_roll<S, 4, MK, THERMAL, REC>;
     if constexpr (!THERMAL)
-        if (cycles == 6) return (const void *)&k_step3_roll<S, 6, MK, THERMAL>;
+        if (cycles == 6) return (const void *)&k_step3_roll<S, 6, MK, THERMAL, REC>;
     return nullptr;
 }
 
 template <typename S, bool THERMAL>
 static const void *roll_fn_mk(const Dom &d, int cycles) {
     switch (medium_kind(d)) {
-    case MK_ERGUN: return roll_fn_t<S, THERMAL, MK_ERGUN>(cycles);
-    case MK_UNIFORM: return roll_fn_t<S, THERMAL, MK_UNIFORM>(cycles);
-    default: return roll_fn_t<S, THERMAL, MK_ANY>(cycles);
+    case MK_ERGUN: return roll_fn_t<S, THERMAL, false, MK_ERGUN>(cycles);
+    case MK_UNIFORM: return roll_fn_t<S, THERMAL, false, MK_UNIFORM>(cycles);
+    default: return roll_fn_t<S, THERMAL, false, MK_ANY>(cycles);
     }
 }
 
@@ -393,6 +409,19 @@ hipError_t launch_step_roll(const Dom &d, int storage, int cycles, hipStream_t s
     const void *fn = storage == ST_F32 ? (d.thermal ? roll_fn_mk<float, true>(d, cycles) : roll_fn_mk<float, false>(d, cycles))
                                        : (d.thermal ? roll_fn_mk<_Float16, true>(d, cycles) : roll_fn_mk<_Float16, false>(d, cycles));
     if (!fn || !roll_domain(d, storage)) return hipErrorInvalidValue;
+    Dom dd = d;
+    RollPlan p = roll_plan(d, cycles);
+    void *args[2] = {&dd, &p};
+    return hipLaunchKernel(fn, dim3((unsigned)(p.strips * p.runs)), dim3(64 * ROLL_ROWS), args, 0, st);
+}
+
+// FP32; a uniform medium takes the kernel of any.
+hipError_t launch_step_roll_rec(const Dom &d, int cycles, hipStream_t st) {
+    const bool ergun = medium_kind(d) == MK_ERGUN;
+    const void *fn = nullptr;
+    if (d.thermal) fn = ergun ? roll_fn_t<float, true, true, MK_ERGUN>(cycles) : roll_fn_t<float, true, true, MK_ANY>(cycles);
+    else fn = ergun ? roll_fn_t<float, false, true, MK_ERGUN>(cycles) : roll_fn_t<float, false, true, MK_ANY>(cycles);
+    if (!fn || !roll_domain(d, ST_F32)) return hipErrorInvalidValue;
     Dom dd = d;
     RollPlan p = roll_plan(d, cycles);
     void *args[2] = {&dd, &p};
