@@ -27,6 +27,12 @@ METRIC = "MLUPS & % of HBM roofline per collide-stream step; adjoint/forward tim
 COUNTERS = os.path.join(ROOT, "profiles", "counters_step_lognormal8192_f32.json")
 
 
+# Cycles per launch of the default passes of the workloads below (lbm_time_blocking names
+# the tile pass, which the remainders of a call and lbm_set_time_blocking take): strips
+# and rolling passes six, with the D2Q5 field four.
+DEFAULT_CYCLES = {"channel": 6, "convection": 4, "batch": 6}
+
+
 def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
@@ -198,10 +204,11 @@ def extras(args):
     s.set_schedule(64, 2, 2, 1)
     tb = s.time_blocking()
     # the launch timing first, as for the headline: it also brings the clocks up
-    launch16 = per_launch_ms(s, tb["cycles_per_pass"])
+    launch16 = per_launch_ms(s, DEFAULT_CYCLES["channel"])
     ms = timed(s, args.steps, args.warmup)
     out["fp16_lognormal_channel"] = {"mlups": round(case.nodes / ms / 1e3, 1), "ms_per_step": round(ms, 4),
                                      "bytes_per_node_per_launch": 36, "time_blocking": tb,
+                                     "cycles_per_launch": DEFAULT_CYCLES["channel"],
                                      "launch_ms": round(launch16, 4),
                                      "roofline": roofline(case.nodes, 36, launch16)}
     del s
@@ -223,7 +230,8 @@ def extras(args):
     tb = s.time_blocking()
     out["convection1024"] = {"mlups": round(case.nodes / ms / 1e3, 1), "ms_per_step": round(ms, 5),
                              "bytes_per_node_per_launch": 104, "time_blocking": tb,
-                             "roofline": roofline(case.nodes, 104, ms * tb["cycles_per_pass"]),
+                             "cycles_per_launch": DEFAULT_CYCLES["convection"],
+                             "roofline": roofline(case.nodes, 104, ms * DEFAULT_CYCLES["convection"]),
                              "note": "working set 113 MB, below the 256 MB Infinity Cache"}
     del s
     torch.cuda.empty_cache()
@@ -254,10 +262,10 @@ def extras(args):
         b = lbm.batch_for_cases(cases, storage=storage, tune_cache=os.environ.get("MRTLBM_TUNE_CACHE"))
         ms = timed(b, args.steps, args.warmup)
         tb = b.time_blocking()
-        per_launch = ms * tb["cycles_per_pass"]
+        per_launch = ms * DEFAULT_CYCLES["batch"]
         out[name] = {"mlups": round(b.nodes / ms / 1e3, 1), "ms_per_step": round(ms, 4), "nodes": b.nodes,
                      "bytes_per_node_per_launch": bpn, "schedule": list(b.schedule()), "time_blocking": tb,
-                     "roofline": roofline(b.nodes, bpn, per_launch)}
+                     "cycles_per_launch": DEFAULT_CYCLES["batch"], "roofline": roofline(b.nodes, bpn, per_launch)}
         del b
         torch.cuda.empty_cache()
     out["adjoint2048"] = adjoint_ratio()
@@ -281,8 +289,8 @@ def adjoint_ratio():
     e[0].record()
     f.step(4000)
     e[1].record()
-    # the same forward in four cycles per pass, which the recomputation does not use
-    mode0 = f.time_blocking()["cycles_per_pass"]
+    # the same forward in tiles of four cycles per pass
+    mode0 = DEFAULT_CYCLES["channel"]
     f.set_time_blocking(4)
     e[6].record()
     f.step(4000)
@@ -305,9 +313,9 @@ def adjoint_ratio():
             "backward_ms": round(bwd, 2), "adjoint_forward_ratio": round(bwd / fwd, 3),
             "forward_cycles_per_pass": mode0,
             "forward_four_cycles_ms": round(fwd4, 2), "adjoint_forward_ratio_four_cycles": round(bwd / fwd4, 3),
-            "note": "backward = recomputation from checkpoints (four cycles per pass, recording u) + "
+            "note": "backward = recomputation from checkpoints (rolling passes of six cycles, recording u) + "
                     "adjoint steps (three per pass); forward_ms in the default mode at this size "
-                    f"({mode0} cycles per pass), forward_four_cycles_ms the same forward in four; the "
+                    f"({mode0} cycles per pass), forward_four_cycles_ms the same forward in tiles of four; the "
                     "recorded forward also copies a checkpoint every 200 steps"}
 
 
@@ -349,7 +357,8 @@ def main():
     log(f"bench: generating the {n}x{n} log-normal porosity field")
     case = I.lognormal_channel(n=n, seed=5, K_ref=1e-6 * 2048.0 ** 2)
     solver = lbm.solver_for_case(case, storage=lbm.FP32_DEV)   # the default cycles per HBM pass
-    cycles = solver.time_blocking()["cycles_per_pass"]
+    strip = n * n > 5 << 20   # the rolling pass serves the sizes below
+    cycles = DEFAULT_CYCLES["channel"]
     # The dominant kernel's own launch duration (HIP events around back-to-back launches),
     # measured first: its ~130 launches also bring the GPU out of the clock state it idles
     # in while the host builds the porosity field (right after that, launches run up to
@@ -360,12 +369,12 @@ def main():
     mlups = case.nodes / (ms * 1e-3) / 1e6
     bytes_per_node = 68  # per pass: 8 FP32 loads + 8 FP32 stores + the FP32 porosity load
     rl = roofline(case.nodes, bytes_per_node, launch_ms)
-    tb = solver.time_blocking()
-    shape = f"64 x {tb['rows']} tiles, {tb['threads']} threads"
-    kname = {4: ("void mrt::k_step4<float", f"k_step4<float> ({shape}): four collide-stream cycles per launch"),
-             3: ("void mrt::k_step3<float", f"k_step3<float> ({shape}): three collide-stream cycles per launch"),
-             2: ("void mrt::k_step2<float", f"k_step2<float> ({shape}): two collide-stream cycles per launch"),
-             1: ("void mrt::k_step<float, false, 0", "k_step<float>: one collide-stream cycle per launch")}[cycles]
+    if strip:
+        kname = ("void mrt::k_step4_strip<float, 6", "k_step4_strip<float, 6> (strips of 128 columns, one wavefront "
+                 "each): six collide-stream cycles per launch")
+    else:
+        kname = ("void mrt::k_step3_roll<float, 6", "k_step3_roll<float, 6> (strips of 64 columns, one workgroup per "
+                 "run of rows): six collide-stream cycles per launch")
     traffic = profiling.traffic_bytes(COUNTERS, kname[0]) if n == 8192 else None
     rl["traffic"] = None if traffic is None else round(traffic / 1e9, 4)
     rl["traffic_unit"] = "GB per launch"
