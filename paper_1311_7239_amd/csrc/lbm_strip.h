@@ -463,8 +463,11 @@ static const void *strip_fn_c(const Dom &d) {
 // in 48-step calls, the tile passes' default against the strip pass, one box): log-normal channels in FP32 from 2^22
 // nodes (2048^2 23.5 against 20.1, 3000^2 46.8 against 37.9, 4096^2 81 against 65,
 // 8192^2 294 against 224; 1750^2 15.2 against 15.7); binary16 storage, whose tile
-// passes move half the bytes, from 6 x 2^20 (channel 2500^2 28.4 against 26.9,
-// 8192^2 274 against 218; 2048^2 18.8 against 20.0); uniform media in FP32, where
+// passes move half the bytes, from 9 x 2^20 (channel 3801 x 3001 46.8 against 44.3,
+// 8191^2 256 against 212; 3001 x 3000 36.4 against 36.6, 2576 x 2614 27.5 against 28.7,
+// 2575 x 2614, whose pairs wrap onto odd columns, 29.1 against 32.3), in uniform media
+// from 2^24 (cavity 4096^2 61.2 against 61.0, 8192^2 233 against 213; 3700^2 49.8
+// against 51.1, 2575 x 2615 25.2 against 29.0); uniform media in FP32, where
 // the tiles load no porosity, from 2^23, where these passes take four cycles too
 // (cavity 4096^2 63.4 against 60.9, 8192^2 243 against 227; 2048^2 17.2 against
 // 19.9); and where at least three quarters of the strips' lanes are columns of
@@ -473,7 +476,8 @@ bool strip_domain(const Dom &d, int storage) {
     const int mk = medium_kind(d);
     const bool per_x = d.bc_x == BC_PERIODIC;
     if (d.thermal || mk == MK_ANY || d.bc_x == BC_NEE || d.bc_y == BC_NEE) return false;
-    const int64_t least = storage == ST_F16 ? (int64_t)6 << 20 : (int64_t)1 << (mk == MK_ERGUN ? 22 : 23);
+    const int64_t M = (int64_t)1 << 20;
+    const int64_t least = storage == ST_F16 ? (mk == MK_ERGUN ? 9 : 16) * M : (mk == MK_ERGUN ? 4 : 8) * M;
     if ((int64_t)d.nx * d.ny < least || d.ny < 64 || (per_x && d.nx < 2 * STRIP_COLS)) return false;
     return 4 * (int64_t)d.nx >= 3 * (int64_t)STRIP_COLS * strip_count(d.nx, per_x, 6);
 }
