@@ -807,9 +807,9 @@ __device__ __forceinline__ void nee_fixup(const Dom &d, const S *__restrict__ fi
     int bx, by;
     if (!nee_wall(d, x, y, bx, by)) return;
     gather_general<S>(d, fin, bx, by, f);
-    if (THERMAL) gather_thermal(d, d.gin, bx, by, false, g);
     const Cell cB = load_cell(d, (int64_t)by * d.pitch + bx);
     const Cell cO = load_cell(d, (int64_t)y * d.pitch + x);
+    if (THERMAL) gather_thermal(d, d.gin, bx, by, false, g);
     nee_rebuild<THERMAL>(d, x, y, cB, cO, f, g);
 }
 
