@@ -332,11 +332,15 @@ int lbm_set_time_blocking(lbm_ctx *c, int32_t cycles_per_pass);
  * of up to ten cycles per launch, and domains of a few hundred nodes by up to
  * 1024; mid-size ones (up to about five million nodes) by rolling passes of
  * six, with the thermal model four cycles; large ones (isothermal, no 1/K or
- * viscosity plane) by strip passes of six and four. The mode reported below
- * fills in where these do not fit. A mode set here (and for the small and the
+ * viscosity plane) by strip passes of six and four. Batches with bounce-back
+ * walls (domains of at least 16 nodes a side, 64 along a periodic axis, and of
+ * at most about five million) step by rolling passes too, without graphs, one
+ * group of domains after another through the passes of a call. The mode
+ * reported below fills in where these do not fit. A mode set here (and for the small and the
  * mid-size ones a tile set by lbm_set_two_cycle_tile, or with on-node walls a
  * launch shape) replaces them. Deep passes run an adjoint's recomputation and
- * its backward sweep too, and the tangent. Same bits as every other pass. */
+ * its backward sweep too, and the tangent; rolling passes its recomputation up
+ * to 2^22 nodes. Same bits as every other pass. */
 
 /* Current cycles per pass, and the workgroup size, tile rows (tiles are 64
  * nodes wide) and grid size of the multi-cycle pass it runs: the four-cycle
