@@ -1159,7 +1159,7 @@ __global__ __launch_bounds__(NT) void k_adjoint_deep(Dom d, DeepPlan p, int C, c
     constexpr int R = (CAP + NT - 1) / NT;
     __shared__ float lds[2 * 8 * CAP];
     __shared__ float ldsg[THERMAL ? 2 * 5 * CAP : 1];
-    const DeepFrame F(d, p, C);
+    const DeepFrame F(d, p, C, (int)blockIdx.x);
     const uint32_t pb4 = (uint32_t)(d.plane * 4);
     const BufRes rg = buf_res(gphi, pb4), rgk = buf_res(gkappa, gkappa ? pb4 : 0u);
     const MediumSrc<MK_ANY> med(d);
@@ -1468,7 +1468,7 @@ __global__ __launch_bounds__(NT) void k_tangent_deep(Dom d, DeepPlan p, int C, i
                                                      const float *__restrict__ dphi, float dnu, float dax, float day) {
     constexpr int R = (CAP + NT - 1) / NT;
     __shared__ float lds[2 * 8 * CAP];
-    const DeepFrame F(d, p, C);
+    const DeepFrame F(d, p, C, (int)blockIdx.x);
     const uint32_t pb4 = (uint32_t)(d.plane * 4);
     const BufRes rin = buf_res(d.fin, 8 * pb4), rout = buf_res(d.fout, 8 * pb4), rd = buf_res(dphi, dphi ? pb4 : 0u);
     const MediumSrc<MK_ANY> med(d);

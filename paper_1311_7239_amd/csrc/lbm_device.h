@@ -732,7 +732,7 @@ __device__ __forceinline__ void load_own_thermal(const Dom &d, const float *__re
 // Whether (x, y) lies on an on-node wall, and the next node inward along the
 // wall normal (diagonally inward at a corner), which is never a wall node
 // (>= 3 nodes per BC_NEE axis).
-__device__ __forceinline__ bool nee_wall(const Dom &d, int x, int y, int &bx, int &by) {
+__host__ __device__ __forceinline__ bool nee_wall(const Dom &d, int x, int y, int &bx, int &by) {
     const bool wx = d.bc_x == BC_NEE && (x == 0 || x == d.nx - 1);
     const bool wy = d.bc_y == BC_NEE && (y == 0 || y == d.ny - 1);
     bx = wx ? (x == 0 ? 1 : d.nx - 2) : x;
