@@ -18,7 +18,7 @@ struct DeepAxis {
     int a, b, lo, hi;
     MRT_HD DeepAxis(int k, int tiles, int n, bool periodic) {
         // tiles of nearly equal size: tile k of T spans [k n / T, (k + 1) n / T)
-        // (products below 2^31: the host admits domains of that size only)
+        // (products below 2^31: deep_fits refuses others)
         a = k * n / tiles;
         b = (k + 1) * n / tiles;
         lo = tiles == 1 || !periodic ? 0 : -(1 << 30);
@@ -154,6 +154,7 @@ static int deep_most_tiles(int n, int bc) { return bc == BC_NEE ? std::max(n / 2
 static bool deep_fits(const Dom &d, const DeepPlan &p, int C) {
     if ((p.tiles_x > 1 && d.bc_x == BC_PERIODIC && C > d.nx) || (p.tiles_y > 1 && d.bc_y == BC_PERIODIC && C > d.ny))
         return false;
+    if ((int64_t)p.tiles_x * d.nx > INT32_MAX || (int64_t)p.tiles_y * d.ny > INT32_MAX) return false;   // DeepAxis
     return C >= 1 && p.tiles_x >= 1 && p.tiles_y >= 1 && p.tiles_x <= deep_most_tiles(d.nx, d.bc_x) &&
            p.tiles_y <= deep_most_tiles(d.ny, d.bc_y);
 }

@@ -63,3 +63,11 @@ def test_tiles_of_one_node_at_an_on_node_wall_are_refused(walk):
                     ((3, 200, N, N, 0, MOST, 2, 16), 0), ((3, 200, N, N, 0, MOST, 1, 16), 1),
                     ((24, 24, W, W, 0, MOST, 16, 16), 1)]:
         assert walk([q])[0][3] == want, q
+
+
+def test_tile_bounds_of_the_longest_axes_stay_in_range(walk):
+    """One-column domains of 1.6 to 2.7 million on-node rows: tile bounds are products of the
+    axis and its number of tiles in 32 bits, beyond which there is no plan."""
+    lines = [(1, ny, P, N, heat, MOST, 0, 0) for heat in (0, 1)
+             for ny in (1_500_000, 1_677_721, 1_700_000, 1_900_000, 2_079_000, 2_097_000, 2_500_000)]
+    _check(walk, lines)
