@@ -342,8 +342,16 @@ int lbm_set_time_blocking(lbm_ctx *c, int32_t cycles_per_pass);
  * its backward sweep too, and the tangent; rolling passes its recomputation up
  * to 2^22 nodes. Same bits as every other pass. */
 
-/* Current cycles per pass, and the workgroup size, tile rows (tiles are 64
- * nodes wide) and grid size of the multi-cycle pass it runs: the four-cycle
+/* The pass that lbm_step(c, n) would launch first on the present state: its
+ * kind and its cycles (host outputs, each may be NULL). A tile pass of a
+ * context with graph steps may be launched as one of a graph's nodes. EINVAL
+ * for n < 1. */
+enum { LBM_PASS_TILES = 0, LBM_PASS_DEEP = 1, LBM_PASS_ROLLING = 2, LBM_PASS_STRIPS = 3 };
+int lbm_next_pass(const lbm_ctx *c, int64_t n, int32_t *kind, int32_t *cycles);
+
+/* Cycles per tile pass (which the passes above may replace: lbm_next_pass
+ * tells), and the workgroup size, tile rows (tiles are 64
+ * nodes wide) and grid size of the multi-cycle tile pass: the four-cycle
  * kernel in mode 4 (768 threads, 26 rows; for a batch the grid is its number
  * of 64 x 26 tiles), the three-cycle kernel in mode 3
  * (single isothermal domains of 2^23 nodes or more: 768 threads, 28 rows;

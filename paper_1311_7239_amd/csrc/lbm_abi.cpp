@@ -486,6 +486,32 @@ int64_t deep_pass_cycles(const lbm_ctx *c, int64_t n) {
 const int kRollCycles[3] = {3, 4, 6};
 int roll_table(int cycles) { return cycles == 6 ? 2 : cycles - 3; }
 
+// The next pass of an lbm_step call with n cycles left: its kind (LBM_PASS_*) and its
+// cycles. Several cycles per pass where they fit; when recording, a pass never steps over
+// a checkpoint time (the checkpoint needs the state there).
+struct Pass {
+    int kind;
+    int64_t cycles;
+};
+
+Pass next_pass(const lbm_ctx *c, int64_t n) {
+    const int64_t deep = deep_pass_cycles(c, n);
+    if (deep > 0) return Pass{LBM_PASS_DEEP, deep};
+    if (c->t == 0) return Pass{LBM_PASS_TILES, 1};   // collide-only first cycle
+    const Domain &D = c->dom[0];
+    const int every = D.desc.ckpt_every;
+    if (c->rec_valid && every > 0) n = std::min<int64_t>(n, every - c->t % every);
+    if (c->roll) {
+        const bool any_medium = c->batch ? !c->batch_uniform : medium_kind(D.dom) == MK_ANY;
+        const int k = roll_cycles(D.dom.thermal != 0, any_medium, n);
+        if (k >= 3) return Pass{LBM_PASS_ROLLING, k};
+    } else if (c->strip) {
+        const int k = strip_cycles(n);
+        return Pass{k >= 4 ? LBM_PASS_STRIPS : LBM_PASS_TILES, k};
+    }
+    return Pass{LBM_PASS_TILES, std::min<int64_t>(n, c->tblock)};
+}
+
 // cycles advanced by one kernel node of the step graph
 int graph_node_steps(const lbm_ctx *c) { return c->tblock; }
 
@@ -716,42 +742,13 @@ int lbm_step(lbm_ctx *c, int64_t n) {
     // velocity of its last collision, u(t - 1) of the final time t, for
     // lbm_reduce's residual; graph replays never end a call.
     while (n > 0) {
-        hipError_t e;
-        const int64_t deep = deep_pass_cycles(c, n);
-        if (deep > 0) {
-            Domain &D = c->dom[0];
-            const Dom d = n == deep ? dom_rec(D, c->cur) : dom_for(D, c->cur);
-            e = launch_step_deep(d, D.desc.storage == LBM_FP16_DEV ? ST_F16 : ST_F32, c->deep, (int)deep, c->t == 0,
-                                 c->stream);
-            if (e != hipSuccess) return device_fail(c, e, "step launch");
-            c->cur ^= 1;
-            c->t += deep;
-            n -= deep;
-            if ((e = checkpoint(c)) != hipSuccess) return device_fail(c, e, "checkpoint copy");
-            continue;
-        }
-        if (c->t == 0) {
-            // collide-only first cycle of every domain
-            for (Domain &D : c->dom) {
-                const Dom d = n == 1 ? dom_rec(D, c->cur) : dom_for(D, c->cur);
-                e = launch_step(d, D.desc.storage == LBM_FP16_DEV ? ST_F16 : ST_F32, SRC_DIRECT, false, c->sched,
-                                c->stream);
-                if (e != hipSuccess) return device_fail(c, e, "step launch");
-            }
-            c->cur ^= 1;
-            c->t = 1;
-            n -= 1;
-            if ((e = checkpoint(c)) != hipSuccess) return device_fail(c, e, "checkpoint copy");
-            continue;
-        }
-        const bool recording = c->rec_valid && c->dom[0].desc.ckpt_every > 0;
-        // several cycles per pass where they fit; when recording, a pass never
-        // steps over a checkpoint time (the checkpoint needs the state there)
-        const bool fused = c->tblock >= 2;
-        const int64_t next_ck = recording ? (c->t / c->dom[0].desc.ckpt_every + 1) * c->dom[0].desc.ckpt_every
-                                          : INT64_MAX;
+        hipError_t e = hipSuccess;
+        Domain &D = c->dom[0];
+        const int st = D.desc.storage == LBM_FP16_DEV ? ST_F16 : ST_F32;
+        const Pass pass = next_pass(c, n);
+        const bool recording = c->rec_valid && D.desc.ckpt_every > 0;
         const int64_t gcyc = graph_cycles(c);
-        if (gcyc > 0 && !recording && !c->roll && !c->strip && n - 1 >= gcyc) {
+        if (gcyc > 0 && pass.kind == LBM_PASS_TILES && c->t > 0 && !recording && !c->roll && !c->strip && n - 1 >= gcyc) {
             if (!c->gexec[c->cur]) {
                 if ((e = build_graph(c, c->cur)) != hipSuccess) return device_fail(c, e, "graph build");
             }
@@ -763,25 +760,21 @@ int lbm_step(lbm_ctx *c, int64_t n) {
             n -= gcyc;
             continue;
         }
-        Domain &D = c->dom[0];
-        const int st = D.desc.storage == LBM_FP16_DEV ? ST_F16 : ST_F32;
-        int cycles = 1;
-        const bool any_medium = c->batch ? !c->batch_uniform : medium_kind(D.dom) == MK_ANY;
-        const int rolled = c->roll ? roll_cycles(D.dom.thermal != 0, any_medium, std::min(n, next_ck - c->t)) : 0;
-        if (c->batch && rolled >= 3) {
+        if (c->batch && pass.kind == LBM_PASS_ROLLING) {
             // one group of domains after another through all its rolling passes
             int64_t left = n;
             int cur = c->cur;
             for (size_t g = 0; g + 1 < c->h_runs[0].first.size(); ++g) {
                 left = n;
                 cur = c->cur;
-                for (int k; (k = roll_cycles(c->batch_thermal, any_medium, left)) >= 3; cur ^= 1) {
-                    left -= k;
-                    const BatchRuns &runs = c->h_runs[roll_table(k)];
-                    e = launch_step_roll_batch(left == 0 ? c->d_doms_rec : c->d_doms,
-                                               c->d_runs[roll_table(k)] + runs.first[g], runs.first[g + 1] - runs.first[g],
-                                               k, cur, c->runs_nt ? 1 : 0, c->storage, c->batch_thermal,
-                                               c->batch_uniform, c->stream);
+                for (Pass p = pass; left > 0 && p.kind == LBM_PASS_ROLLING; p = next_pass(c, left), cur ^= 1) {
+                    left -= p.cycles;
+                    const int q = roll_table((int)p.cycles);
+                    const BatchRuns &runs = c->h_runs[q];
+                    e = launch_step_roll_batch(left == 0 ? c->d_doms_rec : c->d_doms, c->d_runs[q] + runs.first[g],
+                                               runs.first[g + 1] - runs.first[g], (int)p.cycles, cur,
+                                               c->runs_nt ? 1 : 0, c->storage, c->batch_thermal, c->batch_uniform,
+                                               c->stream);
                     if (e != hipSuccess) return device_fail(c, e, "step launch");
                 }
             }
@@ -790,17 +783,21 @@ int lbm_step(lbm_ctx *c, int64_t n) {
             n = left;
             continue;
         }
-        if (rolled >= 3) cycles = rolled;
-        else if (c->strip) cycles = strip_cycles(std::min(n, next_ck - c->t));
-        else if (fused && c->tblock == 4 && n >= 4 && c->t + 4 <= next_ck) cycles = 4;
-        else if (fused && c->tblock >= 3 && n >= 3 && c->t + 3 <= next_ck) cycles = 3;
-        else if (fused && n >= 2 && c->t + 2 <= next_ck) cycles = 2;
+        const int cycles = (int)pass.cycles;
         const bool last = (n == cycles);
         const Dom d = last ? dom_rec(D, c->cur) : dom_for(D, c->cur);
         Dom *doms = last ? c->d_doms_rec : c->d_doms;
-        if (rolled >= 3) {
+        if (pass.kind == LBM_PASS_DEEP) {
+            e = launch_step_deep(d, st, c->deep, cycles, c->t == 0, c->stream);
+        } else if (c->t == 0) {
+            for (Domain &B : c->dom) {
+                e = launch_step(last ? dom_rec(B, c->cur) : dom_for(B, c->cur), st, SRC_DIRECT, false, c->sched,
+                                c->stream);
+                if (e != hipSuccess) break;
+            }
+        } else if (pass.kind == LBM_PASS_ROLLING) {
             e = launch_step_roll(d, st, cycles, c->stream);
-        } else if (c->strip && cycles >= 4) {
+        } else if (pass.kind == LBM_PASS_STRIPS) {
             e = launch_step_strip(d, st, cycles, c->stream);
         } else if (cycles == 4) {
             if (c->batch)
@@ -832,6 +829,15 @@ int lbm_step(lbm_ctx *c, int64_t n) {
         n -= cycles;
         if ((e = checkpoint(c)) != hipSuccess) return device_fail(c, e, "checkpoint copy");
     }
+    return LBM_OK;
+}
+
+int lbm_next_pass(const lbm_ctx *c, int64_t n, int32_t *kind, int32_t *cycles) {
+    if (int rc = check_handle(c)) return rc;
+    if (n < 1) return fail(LBM_EINVAL, "n must be >= 1");
+    const Pass p = next_pass(c, n);
+    if (kind) *kind = p.kind;
+    if (cycles) *cycles = (int32_t)p.cycles;
     return LBM_OK;
 }
 

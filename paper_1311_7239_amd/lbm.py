@@ -96,6 +96,7 @@ def lib():
         L.lbm_set_time_blocking.argtypes = [_vp, ctypes.c_int32]
         L.lbm_set_two_cycle_tile.argtypes = [_vp, ctypes.c_int32, ctypes.c_int32]
         L.lbm_time_blocking.argtypes = [_vp] + [ctypes.POINTER(ctypes.c_int32)] * 4
+        L.lbm_next_pass.argtypes = [_vp, ctypes.c_int64] + [ctypes.POINTER(ctypes.c_int32)] * 2
         _lib = L
     return _lib
 
@@ -290,6 +291,10 @@ class Solver:
     def time_blocking(self):
         return _time_blocking(self._ctx)
 
+    def next_pass(self, n: int = 1):
+        """(kind, cycles) of the pass that step(n) would launch first."""
+        return _next_pass(self._ctx, n)
+
     def schedule(self):
         a, v, b, c = (ctypes.c_int32() for _ in range(4))
         check(lib().lbm_schedule(self._ctx, ctypes.byref(a), ctypes.byref(v), ctypes.byref(b),
@@ -301,6 +306,15 @@ def _time_blocking(ctx):
     v = [ctypes.c_int32() for _ in range(4)]
     check(lib().lbm_time_blocking(ctx, *[ctypes.byref(x) for x in v]))
     return {"cycles_per_pass": v[0].value, "threads": v[1].value, "rows": v[2].value, "grid": v[3].value}
+
+
+PASS_KINDS = ("tiles", "deep", "rolling", "strips")   # LBM_PASS_*
+
+
+def _next_pass(ctx, n):
+    k, c = ctypes.c_int32(), ctypes.c_int32()
+    check(lib().lbm_next_pass(ctx, int(n), ctypes.byref(k), ctypes.byref(c)))
+    return PASS_KINDS[k.value], c.value
 
 
 def _plane(a, device):
@@ -377,6 +391,10 @@ class Batch:
 
     def time_blocking(self):
         return _time_blocking(self._ctx)
+
+    def next_pass(self, n: int = 1):
+        """(kind, cycles) of the pass that step(n) would launch first."""
+        return _next_pass(self._ctx, n)
 
     def schedule(self):
         a, v, b, c = (ctypes.c_int32() for _ in range(4))

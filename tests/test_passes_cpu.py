@@ -1,0 +1,73 @@
+"""Which pass lbm_step launches (tests/plan/pass_driver.cpp on the null device): what
+lbm_next_pass reports is what runs, for every kind of pass, and the passes of a call."""
+import os
+import pathlib
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = pathlib.Path(__file__).resolve().parent.parent
+CSRC = ROOT / "paper_1311_7239_amd" / "csrc"
+BUILD = ROOT / "paper_1311_7239_amd" / "_build"
+OBJECTS = [BUILD / f for f in ("lbm_abi.cpp.o", "lbm_kernels.hip.o", "lbm_adjoint.hip.o")]
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CLANG = pathlib.Path(HIPCC).resolve().parent.parent / "llvm" / "bin" / "clang++"
+P, W, N = 0, 1, 2                       # LBM_PERIODIC, LBM_WALLS, LBM_WALLS_NEE
+UNIFORM, ERGUN, KAPPA = 0, 1, 2         # LBM_MEDIUM_*
+
+pytestmark = pytest.mark.skipif(not (shutil.which(HIPCC) or os.path.exists(HIPCC)) or not CLANG.exists()
+                                or not all(o.exists() for o in OBJECTS), reason="hipcc or kernel objects missing")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("passes")
+    dev_o, exe = tmp / "null_device.o", tmp / "pass_driver"
+    r = subprocess.run([HIPCC, "-x", "hip", "--cuda-host-only", "--offload-arch=gfx950", "-O1", "-std=c++17", "-fPIC",
+                        "-I", str(CSRC), "-c", str(ROOT / "tests" / "sanitize" / "null_device.cpp"), "-o", str(dev_o)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    # linked without the HIP runtime: every HIP symbol resolves to the null device
+    r = subprocess.run([str(CLANG), "-O1", "-std=c++17", "-I", str(ROOT / "include"),
+                        str(ROOT / "tests" / "plan" / "pass_driver.cpp"), str(dev_o), *map(str, OBJECTS), "-lm",
+                        "-o", str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def passes(n, nx, ny, bx=W, by=W, medium=UNIFORM, half=0, heat=0, j=0, every=0, mode=0, t=1, count=1):
+        line = f"{count} {nx} {ny} {bx} {by} {medium} {half} {heat} {j} {every} {mode} {t} {n}\n"
+        r = subprocess.run([str(exe)], input=line, capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        out = r.stdout.split()
+        assert not any(q.endswith("?") for q in out), out
+        return out
+
+    return passes
+
+
+@pytest.mark.parametrize("want,kw", [
+    ("deep", dict(nx=8, ny=64, bx=P)), ("deep", dict(nx=512, ny=512)), ("deep", dict(nx=200, ny=200, bx=N, by=N)),
+    ("deep", dict(nx=300, ny=300, heat=1)), ("rolling", dict(nx=777, ny=1000, bx=P, medium=KAPPA, j=1)),
+    ("rolling", dict(nx=1024, ny=1024, heat=1)), ("rolling", dict(nx=901, ny=601, medium=ERGUN, half=1)),
+    ("strips", dict(nx=8192, ny=8192, bx=P, medium=ERGUN)), ("strips", dict(nx=4099, ny=3001, bx=P, medium=ERGUN, half=1)),
+    ("tiles", dict(nx=2000, ny=2000, bx=N, by=N)), ("rolling", dict(nx=300, ny=200, count=5)),
+    ("rolling", dict(nx=200, ny=200, heat=1, count=27)), ("tiles", dict(nx=200, ny=200, bx=N, by=N, count=3)),
+    ("tiles", dict(nx=512, ny=512, mode=2)), ("tiles", dict(nx=1024, ny=1024, mode=3)),
+    ("tiles", dict(nx=8192, ny=8192, bx=P, medium=ERGUN, mode=4)), ("tiles", dict(nx=300, ny=200, count=5, mode=4)),
+])
+def test_the_reported_pass_is_the_one_launched(driver, want, kw):
+    out = driver(48, **kw)
+    assert all(q.startswith(want) for q in out), out
+    out = driver(49, t=0, **kw)   # with the first cycle, which only deep passes take in
+    assert out[0] == "tiles1" or want == "deep", out
+    assert all(q.startswith(want) for q in out[1:]), out
+
+
+def test_passes_stop_at_checkpoints(driver):
+    for kw in (dict(nx=90, ny=50, bx=P), dict(nx=700, ny=601, medium=ERGUN), dict(nx=2800, ny=2001, medium=ERGUN)):
+        t = 3
+        for q in driver(40, every=11, t=t, **kw):
+            k = int(q.lstrip("adeghilnoprst"))
+            assert t // 11 == (t + k - 1) // 11, (kw, t, q)
+            t += k
+        assert t == 43
