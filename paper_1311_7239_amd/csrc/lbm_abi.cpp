@@ -494,6 +494,27 @@ struct Pass {
     int64_t cycles;
 };
 
+// Whether three or four cycles go through a tile pass where sixes roll or run in strips:
+// once the populations leave the Infinity Cache, such a pass is bound by memory, which
+// tiles read and write in whole lines (us per call of so many steps, the short pass
+// against the tiles, one box):
+//   * strips of four cycles in FP32 from 6 x 2^20 nodes and in uniform media (log-normal
+//     channel 2300^2 100 against 106, 2600^2 136 / 132, 4096^2 336 / 302, 8192^2 1335 /
+//     1128; cavity 3400^2 258 / 201, 4096^2 325 / 269), in binary16 storage in uniform
+//     media (channel 4096^2 259 / 279, cavity 5800^2 532 / 497);
+//   * rolling passes with a 1/K or viscosity plane beyond 5 x 2^20 nodes (2300^2 three
+//     cycles 115 / 98, four 123 / 115, 2890^2 254 / 159 and 266 / 183; others end there:
+//     2048^2 channel 77 / 75 and 83 / 86), heated ones of three from 2^22 nodes (2100^2
+//     142 / 123).
+bool short_pass_in_tiles(const lbm_ctx *c, int64_t cycles) {
+    if (c->batch) return false;
+    const Domain &D = c->dom[0];
+    const int64_t nodes = (int64_t)D.dom.nx * D.dom.ny, M = (int64_t)1 << 20;
+    const int mk = medium_kind(D.dom);
+    if (c->strip) return mk == MK_UNIFORM || (D.desc.storage == LBM_FP32_DEV && nodes >= 6 * M);
+    return D.dom.thermal ? cycles == 3 && nodes >= 4 * M : mk == MK_ANY && nodes > 5 * M;
+}
+
 Pass next_pass(const lbm_ctx *c, int64_t n) {
     const int64_t deep = deep_pass_cycles(c, n);
     if (deep > 0) return Pass{LBM_PASS_DEEP, deep};
@@ -501,15 +522,19 @@ Pass next_pass(const lbm_ctx *c, int64_t n) {
     const Domain &D = c->dom[0];
     const int every = D.desc.ckpt_every;
     if (c->rec_valid && every > 0) n = std::min<int64_t>(n, every - c->t % every);
-    if (c->roll) {
+    int64_t most = c->tblock;   // cycles of a tile pass
+    if (c->roll || c->strip) {
         const bool any_medium = c->batch ? !c->batch_uniform : medium_kind(D.dom) == MK_ANY;
-        const int k = roll_cycles(D.dom.thermal != 0, any_medium, n);
-        if (k >= 3) return Pass{LBM_PASS_ROLLING, k};
-    } else if (c->strip) {
-        const int k = strip_cycles(n);
-        return Pass{k >= 4 ? LBM_PASS_STRIPS : LBM_PASS_TILES, k};
+        const bool thermal = D.dom.thermal != 0;
+        const int k = c->roll ? roll_cycles(thermal, any_medium, n) : strip_cycles(n);
+        // (heated, in a medium of any kind, two tile passes of two cycles are faster than
+        // a rolling one of three and one more: 1000^2 49 us against 52)
+        const bool other = k < (c->roll ? 3 : 4) || (thermal && any_medium && n == 4);
+        if (!other && (k == 6 || !short_pass_in_tiles(c, k)))
+            return Pass{c->roll ? LBM_PASS_ROLLING : LBM_PASS_STRIPS, k};
+        if (!c->batch && (!other || (c->strip && k == 3))) most = k;
     }
-    return Pass{LBM_PASS_TILES, std::min<int64_t>(n, c->tblock)};
+    return Pass{LBM_PASS_TILES, std::min(n, most)};
 }
 
 // cycles advanced by one kernel node of the step graph

@@ -71,3 +71,25 @@ def test_passes_stop_at_checkpoints(driver):
             assert t // 11 == (t + k - 1) // 11, (kw, t, q)
             t += k
         assert t == 43
+
+
+# Passes of three and four cycles beyond the caches: those of tiles, which are faster there.
+@pytest.mark.parametrize("n,want,kw", [
+    (4, "tiles4", dict(nx=8192, ny=8192, bx=P, medium=ERGUN)),
+    (20, "strips6 strips6 tiles4 tiles4", dict(nx=8192, ny=8192, bx=P, medium=ERGUN)),
+    (7, "tiles4 tiles3", dict(nx=3000, ny=3000)), (10, "strips6 tiles4", dict(nx=4096, ny=4096)),
+    (4, "strips4", dict(nx=2300, ny=2300, bx=P, medium=ERGUN)),
+    (4, "strips4", dict(nx=4099, ny=3001, bx=P, medium=ERGUN, half=1)), (4, "tiles4", dict(nx=4200, ny=4200, half=1)),
+    (3, "tiles3", dict(nx=2800, ny=2800, bx=P, medium=KAPPA, j=1)),
+    (8, "tiles4 tiles4", dict(nx=2800, ny=2800, bx=P, medium=KAPPA, j=1)),
+    (10, "rolling6 tiles4", dict(nx=2800, ny=2800, bx=P, medium=KAPPA)),
+    (7, "rolling4 rolling3", dict(nx=777, ny=1000, bx=P, medium=KAPPA, j=1)),
+    (7, "rolling4 rolling3", dict(nx=2048, ny=2048, bx=P, medium=ERGUN)),
+    (4, "tiles2 tiles2", dict(nx=1000, ny=1000, heat=1, medium=KAPPA)),
+    (7, "rolling3 tiles2 tiles2", dict(nx=1000, ny=1000, heat=1, medium=KAPPA)),
+    (7, "rolling4 rolling3", dict(nx=1000, ny=1000, heat=1)), (7, "rolling4 tiles3", dict(nx=2100, ny=2100, heat=1)),
+    (7, "tiles3 tiles3 tiles1", dict(nx=2100, ny=2100, heat=1, medium=KAPPA)),
+    (4, "tiles3 tiles1", dict(nx=3000, ny=3000, mode=3)),
+])
+def test_short_passes_of_large_domains(driver, n, want, kw):
+    assert " ".join(driver(n, **kw)) == want
