@@ -280,6 +280,7 @@ struct lbm_ctx {
     int4 *d_runs[3] = {nullptr, nullptr, nullptr};
     BatchRuns h_runs[3];
     bool runs_nt = false;       // a group of them is larger than the cache
+    bool beyond_cache = false;  // the populations of all domains together are
     // steps replayed from one hand-built HIP graph (0: launch each step);
     // one executable graph per starting buffer parity
     int graph_steps = 0;
@@ -505,9 +506,13 @@ struct Pass {
 //   * rolling passes with a 1/K or viscosity plane beyond 5 x 2^20 nodes (2300^2 three
 //     cycles 115 / 98, four 123 / 115, 2890^2 254 / 159 and 266 / 183; others end there:
 //     2048^2 channel 77 / 75 and 83 / 86), heated ones of three from 2^22 nodes (2100^2
-//     142 / 123).
+//     142 / 123);
+//   * isothermal batches whose states that cache does not hold (60 cavities of 64 to 768
+//     nodes a side, 750 MB: three 270 / 207, four 294 / 239; the 256 of that kind 1334 /
+//     945 and 1405 / 1091; 250 MB: 74 / 76 and 85 / 88; binary16 430 MB 278 / 251 and
+//     300 / 277, 234 MB 133 / 137 and 148 / 153).
 bool short_pass_in_tiles(const lbm_ctx *c, int64_t cycles) {
-    if (c->batch) return false;
+    if (c->batch) return c->beyond_cache && !c->batch_thermal;
     const Domain &D = c->dom[0];
     const int64_t nodes = (int64_t)D.dom.nx * D.dom.ny, M = (int64_t)1 << 20;
     const int mk = medium_kind(D.dom);
@@ -532,7 +537,7 @@ Pass next_pass(const lbm_ctx *c, int64_t n) {
         const bool other = k < (c->roll ? 3 : 4) || (thermal && any_medium && n == 4);
         if (!other && (k == 6 || !short_pass_in_tiles(c, k)))
             return Pass{c->roll ? LBM_PASS_ROLLING : LBM_PASS_STRIPS, k};
-        if (!c->batch && (!other || (c->strip && k == 3))) most = k;
+        if (!other || (c->strip && k == 3)) most = c->batch ? std::min<int64_t>(k, most) : k;
     }
     return Pass{LBM_PASS_TILES, std::min(n, most)};
 }
@@ -1717,6 +1722,9 @@ extern "C" int lbm_create_batch(int32_t n, const lbm_desc *descs, const float *c
     c->d_tiles = (int4 *)(base + B.off_tiles);
     size_t state_bytes = 0;
     for (const Domain &D : c->dom) state_bytes += D.L.f_bytes + D.L.g_bytes;
+    size_t populations = 0;
+    for (const Domain &D : c->dom) populations += 2 * 8 * (size_t)D.L.esize * D.desc.nx * D.desc.ny;
+    c->beyond_cache = populations > kCacheBytes;
     c->h_doms.resize(4 * (size_t)n);
     c->d_doms_rec = c->d_doms + 2 * (size_t)n;
     for (int32_t k = 0; k < n; ++k) {

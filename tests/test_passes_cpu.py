@@ -93,3 +93,20 @@ def test_passes_stop_at_checkpoints(driver):
 ])
 def test_short_passes_of_large_domains(driver, n, want, kw):
     assert " ".join(driver(n, **kw)) == want
+
+
+# The same for batches, by the bytes of all their states (the null device's tuner takes tiles
+# of four cycles, two with the thermal model).
+@pytest.mark.parametrize("n,want,kw", [
+    (3, "tiles3", dict(nx=500, ny=500, count=17)), (4, "tiles4", dict(nx=500, ny=500, count=17)),
+    (5, "tiles3 tiles2", dict(nx=500, ny=500, count=17)), (8, "tiles4 tiles4", dict(nx=500, ny=500, count=17)),
+    (20, "rolling6 rolling6 tiles4 tiles4", dict(nx=500, ny=500, count=17, medium=KAPPA)),
+    (4, "tiles2 tiles2", dict(nx=500, ny=500, count=40, half=1, mode=0, heat=1, medium=KAPPA)),
+    (20, "rolling6 rolling6 rolling4 rolling4", dict(nx=500, ny=500, count=16)),
+    (4, "rolling4", dict(nx=500, ny=500, count=30, half=1)), (4, "tiles4", dict(nx=500, ny=500, count=34, half=1)),
+    (7, "rolling4 rolling3", dict(nx=500, ny=500, count=17, heat=1)),
+    (4, "rolling4", dict(nx=36, ny=40, count=2000)),   # rows of 64 elements, of which 36 count
+    (4, "tiles2 tiles2", dict(nx=200, ny=200, count=9, heat=1, medium=KAPPA)),
+])
+def test_short_passes_of_large_batches(driver, n, want, kw):
+    assert " ".join(driver(n, **kw)) == want
