@@ -468,18 +468,38 @@ int64_t deep_cycles_of(int most, int64_t n) {
     return (n + passes - 1) / passes;
 }
 
-// The same for the next n cycles of a run (0: another pass). Below three cycles
-// the launch and the ring of a larger domain cost more than the other passes (450^2
-// cavity, one step per call: 20 us against 16; 20 x 500: 15 and 15).
+// The same for the next n cycles of a run (0: another pass). One or two cycles are faster
+// in the other passes from some size on, where a tile pass is bound by its launch and a
+// deep one by its ring and its load too (us per call of one, of two steps, deep against
+// tiles, one box: 128^2 cavity 3.9 / 4.4 and 4.9 / 4.8, 160^2 4.6 / 4.4 and 5.5 / 5.1,
+// 256^2 5.6 / 4.8 and 6.6 / 5.1; heated 100^2 4.7 / 5.8 and 5.7 / 6.4, 160^2 6.1 / 5.8
+// and 7.0 / 6.4; one step in binary16 200^2 4.8 / 7.6; on-node walls, 200^2 and 512^2:
+// 1.3 and 2.2 times as fast, equal and equal). So a remainder of one or two after full
+// passes is left to the tiles as well (512^2, eight steps: six and two 22.4, four and
+// four 28.9, tiles 24.4; heated 250^2, eight: 23.0 and 25.1, tiles 25.2; but 400^2 32.4 and
+// 31.4).
 int64_t deep_run_cycles(const lbm_ctx *c, int64_t n) {
     const lbm_desc &d = c->dom[0].desc;
-    return n < 3 && (int64_t)d.nx * d.ny > 65536 ? 0 : deep_cycles_of(c->deep_cycles, n);
+    const int64_t nodes = (int64_t)d.nx * d.ny, most = c->deep_cycles;
+    if (on_node_walls(d)) return n < 3 && nodes > 65536 ? 0 : deep_cycles_of((int)most, n);
+    const bool small = nodes <= (n == 1 && d.storage == LBM_FP16_DEV ? 65536 : 20000);
+    if (n < 3 && !small) return 0;
+    if (n > most && most >= 3 && n % most > 0 && n % most < 3 && nodes > 20000 && (!d.thermal.enabled || nodes <= 65536))
+        return most;
+    return deep_cycles_of((int)most, n);
 }
 
-// And of an lbm_step call with n cycles left: none over a checkpoint.
+// And of an lbm_step call with n cycles left: none over a checkpoint. A call of four
+// steps is as fast or faster in two tile passes of two where they fill the chip (400^2
+// 12.4 deep against 11.6, 500^2 channel 13.6 / 12.8, 350^2 10.2 / 11.2; binary16 400^2
+// 11.3 / 12.4, 500^2 13.8 / 12.6; heated 400^2 15.0 / 15.8).
 int64_t deep_pass_cycles(const lbm_ctx *c, int64_t n) {
-    const int every = c->dom[0].desc.ckpt_every;
-    if (c->rec_valid && every > 0) n = std::min<int64_t>(n, every - c->t % every);
+    const lbm_desc &d = c->dom[0].desc;
+    const bool recording = c->rec_valid && d.ckpt_every > 0;
+    if (recording) n = std::min<int64_t>(n, d.ckpt_every - c->t % d.ckpt_every);
+    if (n == 4 && c->t > 0 && !recording && !d.thermal.enabled && !on_node_walls(d) &&
+        (int64_t)d.nx * d.ny > (d.storage == LBM_FP16_DEV ? 200000 : 140000))
+        return 0;
     return deep_run_cycles(c, n);
 }
 

@@ -58,7 +58,7 @@ def driver(tmp_path_factory):
 def test_the_reported_pass_is_the_one_launched(driver, want, kw):
     out = driver(48, **kw)
     assert all(q.startswith(want) for q in out), out
-    out = driver(49, t=0, **kw)   # with the first cycle, which only deep passes take in
+    out = driver(48 if want == "deep" else 49, t=0, **kw)   # with the first cycle, which only deep passes take in
     assert out[0] == "tiles1" or want == "deep", out
     assert all(q.startswith(want) for q in out[1:]), out
 
@@ -109,4 +109,20 @@ def test_short_passes_of_large_domains(driver, n, want, kw):
     (4, "tiles2 tiles2", dict(nx=200, ny=200, count=9, heat=1, medium=KAPPA)),
 ])
 def test_short_passes_of_large_batches(driver, n, want, kw):
+    assert " ".join(driver(n, **kw)) == want
+
+
+# Small domains: one, two and sometimes four cycles in tiles.
+@pytest.mark.parametrize("n,want,kw", [
+    (1, "deep1", dict(nx=128, ny=128)), (2, "deep2", dict(nx=128, ny=128)), (1, "tiles1", dict(nx=256, ny=256)),
+    (2, "tiles2", dict(nx=200, ny=200, bx=P, medium=ERGUN)), (1, "deep1", dict(nx=200, ny=200, half=1)),
+    (2, "tiles2", dict(nx=250, ny=250, heat=1)), (2, "deep2", dict(nx=100, ny=100, heat=1)),
+    (2, "deep2", dict(nx=200, ny=200, bx=N, by=N)), (2, "tiles1 tiles1", dict(nx=512, ny=512, bx=N, by=N)),
+    (4, "tiles2 tiles2", dict(nx=512, ny=512)), (4, "deep4", dict(nx=300, ny=300)),
+    (7, "deep6 tiles1", dict(nx=512, ny=512)), (8, "deep6 tiles2", dict(nx=500, ny=500, bx=P, medium=ERGUN)),
+    (9, "deep5 tiles2 tiles2", dict(nx=512, ny=512)), (9, "deep9", dict(nx=400, ny=400)),
+    (12, "deep6 deep6", dict(nx=512, ny=512)),
+    (11, "deep6 deep5", dict(nx=100, ny=100)), (1030, "deep515 deep515", dict(nx=8, ny=64, bx=P)),
+])
+def test_short_passes_of_small_domains(driver, n, want, kw):
     assert " ".join(driver(n, **kw)) == want
