@@ -1861,6 +1861,16 @@ int backward_impl(lbm_ctx *c, const float *dL_du, float *dL_dphi, float *dL_dkap
     DeepPlan adeep{};
     int adeep_cycles = 0;
     if (c->deep_cycles > 0) (void)deep_plan(D.dom, (int64_t)L.theta_slots, &adeep, &adeep_cycles);
+    // Not for the one or two steps of a short segment, from some size on (us of a backward
+    // pass of 30 steps, segments of one step and of two, deep against not: channel 128^2
+    // 1.04 and 1.27 times as fast, 200^2 0.79 and 1.14, 500^2 0.88 and 0.99; heated 80^2
+    // 1.05 and 1.40, 128^2 0.94 and 1.23; with parameter gradients 22^2 0.97 and 1.27,
+    // 128^2 0.90 and 1.17, 500^2 0.86 and 0.93; one tile, 16^2 1.16 and 1.38, 27^2 0.90 and
+    // 1.14).
+    const int64_t nodes = (int64_t)d.nx * d.ny;
+    const bool one_step = adeep.tiles_x * adeep.tiles_y == 1 ? th || nodes <= (theta ? 512 : 400)
+                                                             : !theta && nodes <= (th ? 8192 : 16384);
+    const int64_t adeep_least = one_step ? 1 : (nodes <= 160000 ? 2 : 3);
 
     hipError_t e = hipSuccess;
     if (acc) e = launch_fill_zero(acc, sizeof(double) * 4 * (L.theta_slots + 1), st);
@@ -1919,7 +1929,8 @@ int backward_impl(lbm_ctx *c, const float *dL_du, float *dL_dphi, float *dL_dkap
             // backward through the segment (two or three steps per pass in the multi-cycle modes)
             for (int64_t t = s1 - 1; t >= s0;) {
                 const float *ut = urec + (size_t)(t - s0) * rstride;
-                if (const int64_t deep = deep_cycles_of(adeep_cycles, t + 1 - s0); deep > 0) {
+                const int64_t left = t + 1 - s0;
+                if (const int64_t deep = left < adeep_least ? 0 : deep_cycles_of(adeep_cycles, left); deep > 0) {
                     e = launch_adjoint_deep(D.dom, adeep, (int)deep, lam[la], lam[la ^ 1], lamg[la], lamg[la ^ 1], ut,
                                             gphi, gk, acc, st);
                     t -= deep;
@@ -2011,11 +2022,15 @@ extern "C" int lbm_tangent(lbm_ctx *c, const float *dphi, const double *dtheta, 
     int64_t t0 = 0;
     if (c->deep_cycles > 0) {
         // small domains: a segment's state in deep passes that record, then its tangent
-        // in deep passes that read the records
+        // in deep passes that read the records; what is left after the last segment of
+        // three steps step by step
         float *urec = (float *)(D.base + L.off_urec);
         const size_t rstride = 5 * (size_t)L.plane;
         for (; t0 < T;) {
             const int64_t t1 = std::min<int64_t>(t0 + d.ckpt_every, T);
+            // (segments of one step cost twice as much so as step by step, those of two
+            // 1.1 times at 128^2 and 1.2 at 200^2, of three 0.87 and 1.0)
+            if (t1 - t0 < 3) break;
             for (int64_t t = t0, n; t < t1; t += n, p ^= 1) {
                 n = deep_cycles_of(c->deep_cycles, t1 - t);
                 Dom ds = state();

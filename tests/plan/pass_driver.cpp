@@ -8,9 +8,15 @@
 //   t: steps taken before; n: the call
 // Output per line: the passes of lbm_step(n), kind and cycles each, as lbm_next_pass
 // reports them, "?" after one whose launch was of another kind.
+//
+// With the argument "reverse" input lines: nx ny bx by medium heat every steps theta. Output:
+// the launches of deep, rolling and tile passes that recompute in lbm_backward (theta: with
+// parameter gradients), of deep and other adjoint passes, and of deep and other passes of
+// lbm_tangent.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <vector>
 
 #include "lbm.h"
@@ -30,7 +36,44 @@ static void die(const char *what) {
     std::exit(2);
 }
 
-int main() {
+static int reverse() {
+    int nx, ny, bx, by, medium, heat, every, theta;
+    long T;
+    while (std::scanf("%d %d %d %d %d %d %d %ld %d", &nx, &ny, &bx, &by, &medium, &heat, &every, &T, &theta) == 9) {
+        lbm_desc d;
+        lbm_desc_defaults(&d);
+        d.nx = nx; d.ny = ny; d.bc_x = bx; d.bc_y = by; d.nu = 0.1; d.dp = 1.0; d.medium = medium; d.ckpt_every = every;
+        if (heat) {
+            d.thermal.enabled = 1; d.thermal.tau_T = 0.8; d.thermal.Th = 2.0; d.thermal.Tc = 1.0; d.thermal.T0 = 1.5;
+        }
+        std::vector<float> plane((size_t)nx * ny, 0.5f), out(2 * (size_t)nx * ny);
+        size_t bytes = 0;
+        if (lbm_workspace_size(&d, T, &bytes) != LBM_OK) die("workspace size");
+        void *ws = std::aligned_alloc(4096, (bytes + 4095) / 4096 * 4096);
+        lbm_ctx *c = nullptr;
+        if (!ws || lbm_create(&d, plane.data(), plane.data(), ws, bytes, nullptr, &c) != LBM_OK) die("create");
+        if (lbm_step(c, T) != LBM_OK) die("step");
+        const Counts a = Counts::now();
+        const long ad = null_device_launches("k_adjoint_deep"), as = null_device_launches("k_adjoint_step");
+        double th[4];
+        const int rc = theta ? lbm_backward_params(c, out.data(), plane.data(), nullptr, th)
+                             : lbm_backward(c, out.data(), plane.data(), nullptr);
+        if (rc != LBM_OK) die("backward");
+        const Counts b = Counts::now();
+        std::printf("%ld %ld %ld %ld %ld", b.deep - a.deep, b.roll - a.roll,
+                    (b.step - a.step) - (b.deep - a.deep) - (b.roll - a.roll), null_device_launches("k_adjoint_deep") - ad,
+                    null_device_launches("k_adjoint_step") - as);
+        const long td = null_device_launches("k_tangent_deep"), ts = null_device_launches("k_tangent_step");
+        if (!heat && lbm_tangent(c, plane.data(), nullptr, out.data()) != LBM_OK) die("tangent");
+        std::printf(" %ld %ld\n", null_device_launches("k_tangent_deep") - td, null_device_launches("k_tangent_step") - ts);
+        lbm_destroy(c);
+        std::free(ws);
+    }
+    return 0;
+}
+
+int main(int argc, char **argv) {
+    if (argc > 1 && std::strcmp(argv[1], "reverse") == 0) return reverse();
     int count, nx, ny, bx, by, medium, half, heat, j, every, mode;
     long t, n;
     while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %ld %ld", &count, &nx, &ny, &bx, &by, &medium, &half, &heat, &j,

@@ -42,6 +42,14 @@ def driver(tmp_path_factory):
         assert not any(q.endswith("?") for q in out), out
         return out
 
+    def reverse(nx, ny, every, steps, theta=0, bx=P, by=W, medium=ERGUN, heat=0):
+        r = subprocess.run([str(exe), "reverse"], input=f"{nx} {ny} {bx} {by} {medium} {heat} {every} {steps} {theta}\n",
+                           capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        return dict(zip(("rec_deep", "rec_roll", "rec_tiles", "deep", "steps", "tan_deep", "tan_steps"),
+                        map(int, r.stdout.split())))
+
+    passes.reverse = reverse
     return passes
 
 
@@ -126,3 +134,19 @@ def test_short_passes_of_large_batches(driver, n, want, kw):
 ])
 def test_short_passes_of_small_domains(driver, n, want, kw):
     assert " ".join(driver(n, **kw)) == want
+
+
+def test_short_segments_of_the_reverse_and_the_forward_mode(driver):
+    """Deep passes backward and of the tangent, but not for segments too short for them."""
+    r = driver.reverse
+    assert r(300, 300, 1, 12)["deep"] == 0 and r(300, 300, 1, 12)["steps"] == 12
+    assert r(300, 300, 2, 12)["deep"] == 6 and r(500, 500, 2, 12)["deep"] == 0
+    assert r(100, 100, 1, 12)["deep"] == 12 and r(100, 100, 1, 12, theta=1)["deep"] == 0
+    assert r(8, 64, 1, 12, theta=1)["deep"] == 12 and r(27, 27, 1, 12, theta=1)["deep"] == 0
+    assert r(16, 16, 1, 12)["deep"] == 12 and r(300, 300, 3, 12)["deep"] == 4
+    q = r(300, 300, 10, 31, theta=1)   # the last segment is of one step
+    assert q["deep"] == 3 and q["steps"] == 1
+    for nx in (8, 100, 300):
+        assert r(nx, 64, 2, 12)["tan_deep"] == 0 and r(nx, 64, 2, 12)["tan_steps"] == 12
+    q = r(300, 300, 10, 32)
+    assert q["tan_deep"] == 3 and q["tan_steps"] == 2
