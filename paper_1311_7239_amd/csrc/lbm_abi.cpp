@@ -1833,11 +1833,18 @@ int backward_impl(lbm_ctx *c, const float *dL_du, float *dL_dphi, float *dL_dkap
     // four-cycle recording passes in tiles (2048^2: backward 256 ms against 274.5 with
     // three-cycle ones), where they do not roll.
     const bool rec4 = !th && (c->tblock == 4 || (c->tblock == 3 && (int64_t)d.nx * d.ny >= ((int64_t)1 << 22)));
-    // Rolling domains record in rolling passes, up to 2^22 nodes (us per step of a backward
-    // pass, segments of 60, against the tiles: log-normal channel 1024^2 20.3 -> 19.0, 1500^2
-    // 35.0 -> 33.0, 2048^2 64.7 -> 64.3; with a 1/K plane 2000^2 80 -> 73; heated 1500^2 62
-    // -> 57, 2000^2 128 -> 127; but 2200^2 in segments of 61 77.7 -> 80.0).
-    const bool roll_rec = c->roll && (int64_t)d.nx * d.ny <= ((int64_t)1 << 22);
+    // Rolling domains record in rolling passes, up to 2^22 nodes, heated 7 x 2^19 (us per step
+    // of a backward pass, segments of 60, against the tiles: log-normal channel 1024^2 20.3 ->
+    // 19.0, 1500^2 35.0 -> 33.0, 2048^2 64.7 -> 64.3; with a 1/K plane 2000^2 80 -> 73; heated
+    // 1500^2 62 -> 57; but 2200^2 in segments of 61 77.7 -> 80.0, and heated 2040^2 in 24 0.98
+    // times as fast; at 2^22 nodes only in sixes, three and four cycles being 0.97 times as
+    // fast as the tiles' four). With the stress moments that the parameter gradients read, a step
+    // records twice the planes and the tiles, which write them in whole lines, are faster
+    // from 5 x 2^17 nodes (segments of 24, against the tiles: channel 700^2 1.04 times as
+    // fast, 900^2 1.00, 1024^2 0.95, 1500^2 0.87; with a 1/K plane 900^2 1.02, 1500^2 0.91;
+    // heated 700^2 1.04, 900^2 0.98, 1300^2 0.93).
+    const int64_t roll_most = theta ? (int64_t)5 << 17 : (th ? (int64_t)7 << 19 : (int64_t)1 << 22);
+    const bool roll_rec = c->roll && (int64_t)d.nx * d.ny <= roll_most;
     if (dL_dkappa && d.medium != LBM_MEDIUM_PHI_KAPPA) return fail(LBM_EINVAL, "dL_dkappa needs LBM_MEDIUM_PHI_KAPPA");
     if (!c->rec_valid) return fail(LBM_ESTATE, "no recorded trajectory leads to the current state");
     const int64_t T = c->t, k = d.ckpt_every;
@@ -1903,7 +1910,7 @@ int backward_impl(lbm_ctx *c, const float *dL_du, float *dL_dphi, float *dL_dkap
                     e = launch_step_deep_rec(dr, c->deep, (int)deep, t == 0, st);
                     t += deep;
                 } else if (const int rolled = roll_rec && t > 0 ? roll_cycles(th, medium_kind(D.dom) != MK_ERGUN, s1 - t) : 0;
-                           rolled >= 3) {
+                           rolled == 6 || (rolled >= 3 && !rec4)) {
                     e = launch_step_roll_rec(dr, rolled, st);
                     t += rolled;
                 } else if (rec4 && t > 0 && t + 3 < s1) {

@@ -150,3 +150,13 @@ def test_short_segments_of_the_reverse_and_the_forward_mode(driver):
         assert r(nx, 64, 2, 12)["tan_deep"] == 0 and r(nx, 64, 2, 12)["tan_steps"] == 12
     q = r(300, 300, 10, 32)
     assert q["tan_deep"] == 3 and q["tan_steps"] == 2
+
+
+def test_recomputation_with_stress_moments_in_tiles_from_some_size_on(driver):
+    r = driver.reverse
+    for kw in (dict(medium=ERGUN), dict(medium=KAPPA), dict(medium=ERGUN, bx=W, heat=1)):
+        q = r(1500, 1500, 12, 24, theta=1, **kw)
+        assert q["rec_roll"] == 0 and q["rec_tiles"] > 0, kw
+        assert r(1500, 1500, 12, 24, **kw)["rec_roll"] > 0 and r(700, 700, 12, 24, theta=1, **kw)["rec_roll"] > 0
+    assert r(2048, 2048, 4, 24)["rec_roll"] == 0 and r(2048, 2048, 13, 26)["rec_roll"] == 3
+    assert r(2040, 2040, 12, 24, bx=W, heat=1)["rec_roll"] == 0 and r(2040, 2040, 12, 24)["rec_roll"] > 0
