@@ -367,6 +367,14 @@ int lbm_time_blocking(const lbm_ctx *c, int32_t *cycles_per_pass, int32_t *threa
  * below 2^20 nodes). ENOTSUP on batches (autotuned). */
 int lbm_set_two_cycle_tile(lbm_ctx *c, int32_t threads, int32_t rows);
 
+/* Puts back the passes that the context was created with, after
+ * lbm_set_time_blocking, lbm_set_two_cycle_tile or, with on-node walls,
+ * lbm_set_schedule (whose launch shape stays). Setting the mode that
+ * lbm_time_blocking reported does not: it selects the tile passes of that
+ * mode. On a batch the tile table may be uploaded again, which synchronises
+ * the stream. */
+int lbm_default_passes(lbm_ctx *c);
+
 /* Number of steps lbm_step replays from one hand-built HIP graph of kernel
  * nodes (up to 4096, rounded down to a whole number of passes; 0 launches
  * every step separately). Deep, rolling and strip passes are launched

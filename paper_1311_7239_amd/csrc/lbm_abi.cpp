@@ -299,6 +299,11 @@ struct lbm_ctx {
     // in its default mode, a mid-size single domain or a batch: rolling passes
     // (lbm_roll.h), a large single domain: strip passes (lbm_strip.h)
     bool roll = false, strip = false;
+    // these as the context was created with them (lbm_default_passes)
+    struct {
+        int tblock, tb_threads, tb_rows, deep_cycles;
+        bool roll, strip;
+    } made = {};
 };
 
 namespace {
@@ -367,7 +372,8 @@ Source src_now(int64_t t) { return t == 0 ? SRC_DIRECT : SRC_GATHER; }
 std::mutex g_live_mu;
 std::unordered_set<const lbm_ctx *> g_live;
 
-void register_live(const lbm_ctx *c) {
+void register_live(lbm_ctx *c) {
+    c->made = {c->tblock, c->tb_threads, c->tb_rows, c->deep_cycles, c->roll, c->strip};
     std::lock_guard<std::mutex> lock(g_live_mu);
     g_live.insert(c);
 }
@@ -1277,6 +1283,23 @@ int lbm_set_two_cycle_tile(lbm_ctx *c, int32_t threads, int32_t rows) {
     c->tb_rows = rows;
     c->deep_cycles = 0;
     c->roll = false;
+    reset_graphs(c);
+    return LBM_OK;
+}
+
+int lbm_default_passes(lbm_ctx *c) {
+    int rc = check_ctx(c);
+    if (rc) return rc;
+    if (c->batch && c->tb_rows != c->made.tb_rows) {
+        hipError_t e = upload_tiles2(c, c->made.tb_rows);
+        if (e != hipSuccess) return device_fail(c, e, "tile table upload");
+    }
+    c->tblock = c->made.tblock;
+    c->tb_threads = c->made.tb_threads;
+    c->tb_rows = c->made.tb_rows;
+    c->deep_cycles = c->made.deep_cycles;
+    c->roll = c->made.roll;
+    c->strip = c->made.strip;
     reset_graphs(c);
     return LBM_OK;
 }

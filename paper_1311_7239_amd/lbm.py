@@ -96,6 +96,7 @@ def lib():
         L.lbm_set_time_blocking.argtypes = [_vp, ctypes.c_int32]
         L.lbm_set_two_cycle_tile.argtypes = [_vp, ctypes.c_int32, ctypes.c_int32]
         L.lbm_time_blocking.argtypes = [_vp] + [ctypes.POINTER(ctypes.c_int32)] * 4
+        L.lbm_default_passes.argtypes = [_vp]
         L.lbm_next_pass.argtypes = [_vp, ctypes.c_int64] + [ctypes.POINTER(ctypes.c_int32)] * 2
         _lib = L
     return _lib
@@ -288,6 +289,10 @@ class Solver:
     def set_two_cycle_tile(self, threads: int, rows: int):
         check(lib().lbm_set_two_cycle_tile(self._ctx, int(threads), int(rows)))
 
+    def default_passes(self):
+        """Undoes set_time_blocking and set_two_cycle_tile."""
+        check(lib().lbm_default_passes(self._ctx))
+
     def time_blocking(self):
         return _time_blocking(self._ctx)
 
@@ -388,6 +393,10 @@ class Batch:
 
     def set_viscosity_ratio(self, k: int, J: torch.Tensor):
         check(lib().lbm_set_viscosity_ratio(self._ctx, int(k), _ptr(J.contiguous())))
+
+    def default_passes(self):
+        """Undoes set_time_blocking."""
+        check(lib().lbm_default_passes(self._ctx))
 
     def time_blocking(self):
         return _time_blocking(self._ctx)

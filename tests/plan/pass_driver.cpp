@@ -4,7 +4,8 @@
 //
 // Input lines: count nx ny bc_x bc_y medium half heat j_plane every mode t n
 //   count 1: a single domain; above: a batch of count equal domains
-//   mode 0: the default passes; else lbm_set_time_blocking(mode)
+//   mode 0: the default passes; above: lbm_set_time_blocking(mode); below: the same with
+//   -mode, a step, and lbm_default_passes
 //   t: steps taken before; n: the call
 // Output per line: the passes of lbm_step(n), kind and cycles each, as lbm_next_pass
 // reports them, "?" after one whose launch was of another kind.
@@ -97,7 +98,8 @@ int main(int argc, char **argv) {
                                  : lbm_create(&d, plane.data(), plane.data(), ws, bytes, nullptr, &c);
         if (!ws || rc != LBM_OK) die("create");
         if (count > 1 && lbm_set_graph_steps(c, 0) != LBM_OK) die("graph steps");
-        if (mode && lbm_set_time_blocking(c, mode) != LBM_OK) die("mode");
+        if (mode && lbm_set_time_blocking(c, std::abs(mode)) != LBM_OK) die("mode");
+        if (mode < 0 && (lbm_step(c, 1) != LBM_OK || lbm_default_passes(c) != LBM_OK)) die("default passes");
         if (lbm_step(c, t) != LBM_OK) die("step");
         while (n > 0) {
             int32_t kind = -1, cycles = 0;

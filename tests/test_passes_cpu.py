@@ -160,3 +160,16 @@ def test_recomputation_with_stress_moments_in_tiles_from_some_size_on(driver):
         assert r(1500, 1500, 12, 24, **kw)["rec_roll"] > 0 and r(700, 700, 12, 24, theta=1, **kw)["rec_roll"] > 0
     assert r(2048, 2048, 4, 24)["rec_roll"] == 0 and r(2048, 2048, 13, 26)["rec_roll"] == 3
     assert r(2040, 2040, 12, 24, bx=W, heat=1)["rec_roll"] == 0 and r(2040, 2040, 12, 24)["rec_roll"] > 0
+
+
+@pytest.mark.parametrize("kw", [
+    dict(nx=8, ny=64, bx=P), dict(nx=512, ny=512), dict(nx=200, ny=200, bx=N, by=N), dict(nx=1024, ny=1024, heat=1),
+    dict(nx=2900, ny=2700, bx=P, medium=ERGUN), dict(nx=300, ny=200, count=5), dict(nx=200, ny=200, heat=1, count=9),
+    dict(nx=2000, ny=2000, bx=N, by=N),
+])
+def test_default_passes_come_back_after_a_mode(driver, kw):
+    want = driver(23, t=2, **kw)
+    modes = [1] if N in (kw.get("bx"), kw.get("by")) else [1, 2] if "heat" in kw else [1, 2, 3, 4]
+    for mode in modes:
+        assert all(q[:5] == "tiles" for q in driver(23, t=2, mode=mode, **kw))
+        assert driver(23, mode=-mode, **kw) == want   # t = 1 and the step in the mode
