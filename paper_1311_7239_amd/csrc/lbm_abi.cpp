@@ -1397,7 +1397,9 @@ bool batch_is_uniform(int32_t n, const lbm_desc *descs) {
     return true;
 }
 
-// Both state buffers of a domain
+// The measure of a domain's two state buffers by which batches are grouped: the populations
+// and the room of a D2Q5 field, also where there is none (then 13/8 of the populations in
+// FP32: 448 MB by this measure are 276 MB of them).
 size_t state_bytes_of(const lbm_desc &d) {
     const Layout L = make_layout(d, 0);
     return 2 * (L.f_bytes + L.g_bytes);
@@ -1406,7 +1408,7 @@ size_t state_bytes_of(const lbm_desc &d) {
 // The groups of domains (group g from first[g] on) that a batch steps in rolling passes,
 // one group after another through all the passes of a call: nearly equal shares of it
 // that the 256 MB Infinity Cache serves. us per step of the whole batch, in groups of at
-// most 128 / 232 / 448 MB and in one: 60 heated cavities of 300 to 768 nodes a side 137
+// most 128 / 232 / 448 MB by that measure and in one: 60 heated cavities of 300 to 768 nodes a side 137
 // / 120 / 155 / 186 (in tiles 197); 16 cavities of 1000^2, whose re-read state the cache
 // serves in part, 89 / 72 / 64 / 70 (tiles 70). Binary16 flow is not bound by memory:
 // 60 cavities 62 / 53 / 54 / 45 (tiles 54).

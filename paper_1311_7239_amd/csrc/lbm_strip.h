@@ -451,10 +451,13 @@ static const void *strip_fn_c(const Dom &d) {
         if constexpr (sizeof(S) == 2)
             if (odd) return strip_fn_t<S, C, MK_ERGUN, true>(nt, last);
         return strip_fn_t<S, C, MK_ERGUN, false>(nt, last);
-    case MK_UNIFORM:
-        if constexpr (sizeof(S) == 2)
-            if (odd) return strip_fn_t<S, C, MK_UNIFORM, true>(nt, last);
-        return strip_fn_t<S, C, MK_UNIFORM, false>(nt, last);
+    case MK_UNIFORM:   // (four cycles go through tiles)
+        if constexpr (C == 6) {
+            if constexpr (sizeof(S) == 2)
+                if (odd) return strip_fn_t<S, C, MK_UNIFORM, true>(nt, last);
+            return strip_fn_t<S, C, MK_UNIFORM, false>(nt, last);
+        }
+        return nullptr;
     default: return nullptr;
     }
 }
@@ -482,8 +485,8 @@ bool strip_domain(const Dom &d, int storage) {
     return 4 * (int64_t)d.nx >= 3 * (int64_t)STRIP_COLS * strip_count(d.nx, per_x, 6);
 }
 
-// Cycles of the next pass with n left (4 and 6: strips; 1 to 3: tiles): sixes, and
-// fours and a three where they come out even.
+// Cycles of the next pass with n left (6: strips; 4: strips or tiles, whichever the caller
+// finds faster; 1 to 3: tiles): sixes, and fours and a three where they come out even.
 int strip_cycles(int64_t n) {
     static const int next[12] = {0, 1, 2, 3, 4, 3, 6, 4, 4, 6, 6, 4};
     return n >= 12 ? 6 : next[n];
