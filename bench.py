@@ -27,12 +27,6 @@ METRIC = "MLUPS & % of HBM roofline per collide-stream step; adjoint/forward tim
 COUNTERS = os.path.join(ROOT, "profiles", "counters_step_lognormal8192_f32.json")
 
 
-# Cycles per launch of the default passes of the workloads below (lbm_time_blocking names
-# the tile pass, which the remainders of a call and lbm_set_time_blocking take): strips
-# and rolling passes six, with the D2Q5 field four.
-DEFAULT_CYCLES = {"channel": 6, "convection": 4, "batch": 6}
-
-
 def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
@@ -74,6 +68,15 @@ def per_launch_ms(stepper, cycles, launches=20, reps=3):
     long = min(call(cycles * (launches + 1)) for _ in range(reps))
     short = min(call(cycles) for _ in range(reps))
     return (long - short) / launches
+
+
+def repeated_pass(stepper):
+    """{"kind", "cycles"} of the pass that long calls repeat (lbm_next_pass; the first cycle, which
+    differs, is stepped here where it is still to come)."""
+    if stepper.time == 0:
+        stepper.step(1)
+    kind, cycles = stepper.next_pass(96)
+    return {"kind": kind, "cycles": cycles}
 
 
 def roofline(nodes, bytes_per_node, ms):
@@ -202,13 +205,13 @@ def extras(args):
     # FP16-deviation storage on the headline workload (its default cycles per pass)
     s = lbm.solver_for_case(case, storage=lbm.FP16_DEV)
     s.set_schedule(64, 2, 2, 1)
-    tb = s.time_blocking()
+    tb, rp = s.time_blocking(), repeated_pass(s)
     # the launch timing first, as for the headline: it also brings the clocks up
-    launch16 = per_launch_ms(s, DEFAULT_CYCLES["channel"])
+    launch16 = per_launch_ms(s, rp["cycles"])
     ms = timed(s, args.steps, args.warmup)
     out["fp16_lognormal_channel"] = {"mlups": round(case.nodes / ms / 1e3, 1), "ms_per_step": round(ms, 4),
                                      "bytes_per_node_per_launch": 36, "time_blocking": tb,
-                                     "cycles_per_launch": DEFAULT_CYCLES["channel"],
+                                     "pass": rp, "cycles_per_launch": rp["cycles"],
                                      "launch_ms": round(launch16, 4),
                                      "roofline": roofline(case.nodes, 36, launch16)}
     del s
@@ -220,6 +223,7 @@ def extras(args):
     ms = timed(s, 20000, 2000)
     out["cavity512"] = {"mlups": round(case.nodes / ms / 1e3, 1), "ms_per_step": round(ms, 5),
                         "bytes_per_node_per_launch": 64, "time_blocking": s.time_blocking(),
+                        "pass": repeated_pass(s),
                         "note": "working set 34 MB, below the 256 MB Infinity Cache"}
     del s
     log("bench: 1024^2 natural convection (D2Q8 + D2Q5)")
@@ -227,11 +231,11 @@ def extras(args):
     s = lbm.solver_for_case(case)
     s.set_graph_steps(64)
     ms = timed(s, 4000, 500)
-    tb = s.time_blocking()
+    tb, rp = s.time_blocking(), repeated_pass(s)
     out["convection1024"] = {"mlups": round(case.nodes / ms / 1e3, 1), "ms_per_step": round(ms, 5),
                              "bytes_per_node_per_launch": 104, "time_blocking": tb,
-                             "cycles_per_launch": DEFAULT_CYCLES["convection"],
-                             "roofline": roofline(case.nodes, 104, ms * DEFAULT_CYCLES["convection"]),
+                             "pass": rp, "cycles_per_launch": rp["cycles"],
+                             "roofline": roofline(case.nodes, 104, ms * rp["cycles"]),
                              "note": "working set 113 MB, below the 256 MB Infinity Cache"}
     del s
     torch.cuda.empty_cache()
@@ -252,6 +256,7 @@ def extras(args):
     out["table1_batch27_thermal"] = {"mlups": round(b.nodes / ms / 1e3, 1), "ms_per_step": round(ms, 5),
                                      "nodes": b.nodes, "bytes_per_node_per_launch": 104,
                                      "schedule": list(b.schedule()), "time_blocking": b.time_blocking(),
+                                     "pass": repeated_pass(b),
                                      "note": "120^2, 200^2, 250^2 cavities of Sec. 3.4; D2Q8 + D2Q5"}
     del b
     torch.cuda.empty_cache()
@@ -261,11 +266,11 @@ def extras(args):
         # MRTLBM_TUNE_CACHE: optional autotuner cache file (tuned afresh without it)
         b = lbm.batch_for_cases(cases, storage=storage, tune_cache=os.environ.get("MRTLBM_TUNE_CACHE"))
         ms = timed(b, args.steps, args.warmup)
-        tb = b.time_blocking()
-        per_launch = ms * DEFAULT_CYCLES["batch"]
+        tb, rp = b.time_blocking(), repeated_pass(b)
+        per_launch = ms * rp["cycles"]
         out[name] = {"mlups": round(b.nodes / ms / 1e3, 1), "ms_per_step": round(ms, 4), "nodes": b.nodes,
                      "bytes_per_node_per_launch": bpn, "schedule": list(b.schedule()), "time_blocking": tb,
-                     "cycles_per_launch": DEFAULT_CYCLES["batch"], "roofline": roofline(b.nodes, bpn, per_launch)}
+                     "pass": rp, "cycles_per_launch": rp["cycles"], "roofline": roofline(b.nodes, bpn, per_launch)}
         del b
         torch.cuda.empty_cache()
     out["adjoint2048"] = adjoint_ratio()
@@ -290,7 +295,7 @@ def adjoint_ratio():
     f.step(4000)
     e[1].record()
     # the same forward in tiles of four cycles per pass
-    mode0 = DEFAULT_CYCLES["channel"]
+    mode0 = repeated_pass(f)["cycles"]
     f.set_time_blocking(4)
     e[6].record()
     f.step(4000)
@@ -356,9 +361,9 @@ def main():
     n = args.n
     log(f"bench: generating the {n}x{n} log-normal porosity field")
     case = I.lognormal_channel(n=n, seed=5, K_ref=1e-6 * 2048.0 ** 2)
-    solver = lbm.solver_for_case(case, storage=lbm.FP32_DEV)   # the default cycles per HBM pass
-    strip = n * n > 5 << 20   # the rolling pass serves the sizes below
-    cycles = DEFAULT_CYCLES["channel"]
+    solver = lbm.solver_for_case(case, storage=lbm.FP32_DEV)   # the default passes
+    rp = repeated_pass(solver)
+    cycles = rp["cycles"]
     # The dominant kernel's own launch duration (HIP events around back-to-back launches),
     # measured first: its ~130 launches also bring the GPU out of the clock state it idles
     # in while the host builds the porosity field (right after that, launches run up to
@@ -369,16 +374,16 @@ def main():
     mlups = case.nodes / (ms * 1e-3) / 1e6
     bytes_per_node = 68  # per pass: 8 FP32 loads + 8 FP32 stores + the FP32 porosity load
     rl = roofline(case.nodes, bytes_per_node, launch_ms)
-    if strip:
-        kname = ("void mrt::k_step4_strip<float, 6", "k_step4_strip<float, 6> (strips of 128 columns, one wavefront "
-                 "each): six collide-stream cycles per launch")
-    else:
-        kname = ("void mrt::k_step3_roll<float, 6", "k_step3_roll<float, 6> (strips of 64 columns, one workgroup per "
-                 "run of rows): six collide-stream cycles per launch")
+    kname = {"strips": (f"void mrt::k_step4_strip<float, {cycles}", f"k_step4_strip<float, {cycles}> (strips of 128 "
+                        "columns, one wavefront each)"),
+             "rolling": (f"void mrt::k_step3_roll<float, {cycles}", f"k_step3_roll<float, {cycles}> (strips of 64 "
+                         "columns, one workgroup per run of rows)"),
+             "deep": ("void mrt::k_step_deep<float", "k_step_deep<float> (one workgroup per tile)"),
+             "tiles": (f"void mrt::k_step{cycles if cycles > 1 else ''}<float", "tiles of 64 columns")}[rp["kind"]]
     traffic = profiling.traffic_bytes(COUNTERS, kname[0]) if n == 8192 else None
     rl["traffic"] = None if traffic is None else round(traffic / 1e9, 4)
     rl["traffic_unit"] = "GB per launch"
-    rl["kernel"] = kname[1]
+    rl["kernel"] = f"{kname[1]}: {cycles} collide-stream cycles per launch"
     rl["algorithmic_bytes_per_launch"] = case.nodes * bytes_per_node
     rl["launch_ms"] = round(launch_ms, 4)
     rl["launch_timing"] = ("HIP events on the launch stream: 21-pass call minus 1-pass call, 20 back-to-back "
@@ -400,11 +405,11 @@ def main():
         "vs_baseline": None,
         "dtype": "f32",
         "data": "synthetic",
-        "config": {"time_blocking": solver.time_blocking(),
+        "config": {"pass": rp, "time_blocking": solver.time_blocking(),
                    "workload": f"log-normal porous channel {n}x{n}: x periodic, walls in y, per-cell "
                                "porosity (log-normal, sigma 0.5, correlation 64, seed 5) with Ergun K and "
                                f"F_phi, tau 0.8, FP32 deviation storage, forward steps, {cycles} cycles per "
-                               "HBM pass",
+                               "launch",
                    "nodes": case.nodes, "schedule": list(solver.schedule())},
         "roofline": rl,
         "state_check": {"mass": mass, "residual": res},
