@@ -332,15 +332,18 @@ int lbm_set_time_blocking(lbm_ctx *c, int32_t cycles_per_pass);
  * of up to ten cycles per launch, and domains of a few hundred nodes by up to
  * 1024; mid-size ones (up to about five million nodes) by rolling passes of
  * six, with the thermal model four cycles; large ones (isothermal, no 1/K or
- * viscosity plane) by strip passes of six and four. Batches with bounce-back
+ * viscosity plane) by strip passes of six. Batches with bounce-back
  * walls (domains of at least 16 nodes a side, 64 along a periodic axis, and of
  * at most about five million) step by rolling passes too, without graphs, one
- * group of domains after another through the passes of a call. The mode
- * reported below fills in where these do not fit. A mode set here (and for the small and the
- * mid-size ones a tile set by lbm_set_two_cycle_tile, or with on-node walls a
- * launch shape) replaces them. Deep passes run an adjoint's recomputation and
- * its backward sweep too, and the tangent; rolling passes its recomputation up
- * to 2^22 nodes. Same bits as every other pass. */
+ * group of domains after another through the passes of a call. The few cycles
+ * that such passes leave of a call run in shorter ones or in tile passes,
+ * whichever are faster at the size; lbm_next_pass tells. A mode set here (and
+ * for the small and the mid-size ones a tile set by lbm_set_two_cycle_tile, or
+ * with on-node walls a launch shape) replaces them until lbm_default_passes.
+ * Deep passes run an adjoint's recomputation and its backward sweep too, and
+ * the tangent, for segments of some steps; rolling passes its recomputation,
+ * up to 2^22 nodes and with parameter gradients up to 655,360. Same bits as
+ * every other pass. */
 
 /* The pass that lbm_step(c, n) would launch first on the present state: its
  * kind and its cycles (host outputs, each may be NULL). A tile pass of a

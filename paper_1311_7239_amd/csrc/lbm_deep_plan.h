@@ -166,7 +166,7 @@ static bool deep_fits(const Dom &d, const DeepPlan &p, int C) {
 //     32 x 32 0.89 alone against 0.84 on 256 tiles), 640 with the D2Q5 field
 //     (8 x 64: 3.8 against 1.05) and 512 with on-node walls, whose rebuilt nodes
 //     double a wavefront's arithmetic (7.6 against 1.10; 24 x 32 alone 1.67, tiled
-//     1.12). 1024 cycles at most, so that no launch holds the chip for long.
+//     1.01). 1024 cycles at most, so that no launch holds the chip for long.
 //   * Else one tile per CU, as square as they come, and the most cycles up to 10
 //     that its frame holds (128^2 lid cavity: 2.5 against 0.98, 256^2 2.6 against
 //     1.42, 512^2 3.1 against 2.5, 600 x 500 3.8 against 3.1; convection 200^2 3.2

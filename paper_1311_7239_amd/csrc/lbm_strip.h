@@ -14,13 +14,13 @@
 // launch and fewer collisions are redundant: a strip's outer C columns on each
 // side (128 / 116 for C = 6), and on average C - 1 rows at its ends.
 //
-// What bounds it: vector issue. At 8192^2 (FP32, Ergun medium, six cycles) a row of
-// a strip takes 1205 vector instructions for 696 node updates' 64 lanes: 122 per
-// update with the redundant ones, against 139 in the four-cycle tiles, and a
-// cycle moves 14 bytes per node instead of 20. 224 us per step against 294, 74% of
-// the issue rate at 2.4 GHz. Two columns per lane and six cycles are what 168
-// registers hold (three wavefronts per SIMD); four cycles move a half more bytes
-// and took 295 us, eight need two wavefronts per SIMD and a wider ring (272 us).
+// What bounds it: vector issue. At 8192^2 (FP32, Ergun medium, six cycles) a launch
+// issues 7.5e8 vector instructions, 119 per node update with the redundant ones against
+// 143 in the four-cycle tiles: 1.22 ms at 2.4 GHz, of the 1.30 that it takes, and a
+// cycle moves 14 bytes per node instead of 20. 224 us per step against 294 (217 on
+// another box). Two columns per lane and six cycles are what 168 registers hold
+// (three wavefronts per SIMD); four cycles move a half more bytes and took 295 us, eight
+// need two wavefronts per SIMD and a wider ring (272 us).
 #pragma once
 
 #include <type_traits>

@@ -110,7 +110,7 @@ def sq_summary(counters_csv, out_txt, command, kernel_prefix="void mrt::k_step")
 def traffic_bytes(summary_json, kernel_name=None):
     """HBM bytes per dispatch of the step kernel from a counters summary, or None if the
     kernel sources changed since the counters were taken. kernel_name: the full name or a
-    prefix of it (the first match); None takes the most dispatched kernel."""
+    prefix of it (the most dispatched match); None takes the most dispatched kernel."""
     p = pathlib.Path(summary_json)
     if not p.exists():
         return None
@@ -120,7 +120,8 @@ def traffic_bytes(summary_json, kernel_name=None):
     if kernel_name:
         k = s["kernels"].get(kernel_name)
         if k is None:
-            k = next((v for n, v in s["kernels"].items() if n.startswith(kernel_name)), None)
+            k = max((v for n, v in s["kernels"].items() if n.startswith(kernel_name)),
+                    key=lambda v: v["dispatches"], default=None)
     else:
         k = max(s["kernels"].values(), key=lambda v: v["dispatches"])
     if not k or k["write_kib"] is None or not s["fetch_scale"] or not s["write_scale"]:
