@@ -529,10 +529,11 @@ struct Pass {
 //     channel 2300^2 100 against 106, 2600^2 136 / 132, 4096^2 336 / 302, 8192^2 1335 /
 //     1128; cavity 3400^2 258 / 201, 4096^2 325 / 269), in binary16 storage in uniform
 //     media (channel 4096^2 259 / 279, cavity 5800^2 532 / 497);
-//   * rolling passes with a 1/K or viscosity plane beyond 5 x 2^20 nodes (2300^2 three
-//     cycles 115 / 98, four 123 / 115, 2890^2 254 / 159 and 266 / 183; others end there:
-//     2048^2 channel 77 / 75 and 83 / 86), heated ones of three from 2^22 nodes (2100^2
-//     142 / 123);
+//   * rolling passes of three cycles beyond 2,500,000 nodes (1700^2 43 / 44 and 2048^2 channel
+//     77 / 75 in repeated calls, binary16 with a 1/K plane 63 / 60; on a new state, 1221 x
+//     2126, one cycle and three 157 / 146), and with a 1/K or viscosity plane of three
+//     and four beyond 5 x 2^20 (2300^2 115 / 98 and 123 / 115, 2890^2 254 / 159 and 266 /
+//     183); heated ones of three from 2^22 nodes (2100^2 142 / 123);
 //   * isothermal batches whose states that cache does not hold (60 cavities of 64 to 768
 //     nodes a side, 750 MB: three 270 / 207, four 294 / 239; the 256 of that kind 1334 /
 //     945 and 1405 / 1091; 250 MB: 74 / 76 and 85 / 88; binary16 430 MB 278 / 251 and
@@ -543,7 +544,8 @@ bool short_pass_in_tiles(const lbm_ctx *c, int64_t cycles) {
     const int64_t nodes = (int64_t)D.dom.nx * D.dom.ny, M = (int64_t)1 << 20;
     const int mk = medium_kind(D.dom);
     if (c->strip) return mk == MK_UNIFORM || (D.desc.storage == LBM_FP32_DEV && nodes >= 6 * M);
-    return D.dom.thermal ? cycles == 3 && nodes >= 4 * M : mk == MK_ANY && nodes > 5 * M;
+    if (D.dom.thermal) return cycles == 3 && nodes >= 4 * M;
+    return cycles == 3 ? nodes > 2500000 : mk == MK_ANY && nodes > 5 * M;
 }
 
 Pass next_pass(const lbm_ctx *c, int64_t n) {
@@ -1935,7 +1937,7 @@ int backward_impl(lbm_ctx *c, const float *dL_du, float *dL_dphi, float *dL_dkap
                     e = launch_step_deep_rec(dr, c->deep, (int)deep, t == 0, st);
                     t += deep;
                 } else if (const int rolled = roll_rec && t > 0 ? roll_cycles(th, medium_kind(D.dom) != MK_ERGUN, s1 - t) : 0;
-                           rolled == 6 || (rolled >= 3 && !rec4)) {
+                           rolled == 6 || (rolled >= 3 && !rec4 && !(rolled == 3 && short_pass_in_tiles(c, 3)))) {
                     e = launch_step_roll_rec(dr, rolled, st);
                     t += rolled;
                 } else if (rec4 && t > 0 && t + 3 < s1) {

@@ -92,7 +92,9 @@ def test_passes_stop_at_checkpoints(driver):
     (8, "tiles4 tiles4", dict(nx=2800, ny=2800, bx=P, medium=KAPPA, j=1)),
     (10, "rolling6 tiles4", dict(nx=2800, ny=2800, bx=P, medium=KAPPA)),
     (7, "rolling4 rolling3", dict(nx=777, ny=1000, bx=P, medium=KAPPA, j=1)),
-    (7, "rolling4 rolling3", dict(nx=2048, ny=2048, bx=P, medium=ERGUN)),
+    (7, "rolling4 tiles3", dict(nx=2048, ny=2048, bx=P, medium=ERGUN)),
+    (3, "tiles3", dict(nx=1221, ny=2126, medium=ERGUN)), (3, "rolling3", dict(nx=1221, ny=2000, medium=ERGUN)),
+    (3, "tiles3", dict(nx=1700, ny=1700, half=1)),
     (4, "tiles2 tiles2", dict(nx=1000, ny=1000, heat=1, medium=KAPPA)),
     (7, "rolling3 tiles2 tiles2", dict(nx=1000, ny=1000, heat=1, medium=KAPPA)),
     (7, "rolling4 rolling3", dict(nx=1000, ny=1000, heat=1)), (7, "rolling4 tiles3", dict(nx=2100, ny=2100, heat=1)),
@@ -158,6 +160,7 @@ def test_recomputation_with_stress_moments_in_tiles_from_some_size_on(driver):
         q = r(1500, 1500, 12, 24, theta=1, **kw)
         assert q["rec_roll"] == 0 and q["rec_tiles"] > 0, kw
         assert r(1500, 1500, 12, 24, **kw)["rec_roll"] > 0 and r(700, 700, 12, 24, theta=1, **kw)["rec_roll"] > 0
+    assert r(1900, 1900, 4, 24)["rec_roll"] == 5   # the first segment has three cycles after t = 0
     assert r(2048, 2048, 4, 24)["rec_roll"] == 0 and r(2048, 2048, 13, 26)["rec_roll"] == 3
     assert r(2040, 2040, 12, 24, bx=W, heat=1)["rec_roll"] == 0 and r(2040, 2040, 12, 24)["rec_roll"] > 0
 
