@@ -296,6 +296,7 @@ struct lbm_ctx {
     // pass or a tile
     DeepPlan deep{1, 1};
     int deep_cycles = 0;
+    bool deep_steps = true;     // lbm_step takes it, not the adjoint and the tangent alone
     // in its default mode, a mid-size single domain or a batch: rolling passes
     // (lbm_roll.h), a large single domain: strip passes (lbm_strip.h)
     bool roll = false, strip = false;
@@ -474,6 +475,39 @@ int64_t deep_cycles_of(int most, int64_t n) {
     return (n + passes - 1) / passes;
 }
 
+// Where only the adjoint and the tangent take the deep pass of a plan (us per step in long
+// calls, deep against the other pass, one box): heated domains whose plan holds five cycles,
+// which roll (with porosity 445^2 3.65 / 3.53, 600 x 330 3.81 / 3.54, in binary16 445^2 3.81 /
+// 3.68); uniform media in binary16 above 250,000 nodes whose two-cycle tiles are one round of
+// workgroups (437 x 577 2.89 / 2.78, 505^2 2.97 / 2.87; 500^2 2.84 / 2.87, 520 x 510 2.90 /
+// 3.28); heated FP32 domains with on-node walls in y alone, whose one-cycle
+// pass gathers two rows only node by node (557 x 1501 14.6 / 14.2; 900^2 13.6 / 16.3).
+bool deep_steps_pay(const lbm_ctx *c) {
+    const Domain &D = c->dom[0];
+    const lbm_desc &d = D.desc;
+    const int64_t nodes = (int64_t)d.nx * d.ny;
+    const bool heat = d.thermal.enabled != 0, half = d.storage == LBM_FP16_DEV;
+    if (on_node_walls(d)) return !(heat && !half && d.bc_x == LBM_PERIODIC && nodes > 820000);
+    if (heat) return c->deep_cycles > 5;
+    int tx, ty;
+    step2_tiles(d.nx, d.ny, 8, &tx, &ty);
+    return !(half && medium_kind(D.dom) == MK_UNIFORM && nodes > 250000 && tx * ty <= 512);
+}
+
+// Whether four steps are faster in two tile passes of two than in a deep pass, which is where
+// the tiles fill the chip (us, deep against tiles, one box): from 140,000 nodes (400^2 12.4 /
+// 11.6, 500^2 channel 13.6 / 12.8; 350^2 10.2 / 11.2), in binary16 from 200,000 (500^2 13.8 /
+// 12.6; 400^2 11.3 / 12.4), heated from 80,000 (317 x 271 13.8 / 12.7, 300^2 13.9 / 13.2;
+// 250^2 12.7 / 12.9), there in FP32 and uniform media to 125,000 only (400^2 15.0 / 15.5; with
+// porosity 15.2 / 14.7).
+bool four_in_tiles(const lbm_ctx *c) {
+    const Domain &D = c->dom[0];
+    const int64_t nodes = (int64_t)D.desc.nx * D.desc.ny;
+    const bool half = D.desc.storage == LBM_FP16_DEV;
+    if (!D.desc.thermal.enabled) return nodes > (half ? 200000 : 140000);
+    return nodes > 80000 && (half || nodes <= 125000 || medium_kind(D.dom) != MK_UNIFORM);
+}
+
 // The same for the next n cycles of a run (0: another pass). One or two cycles are faster
 // in the other passes from some size on, where a tile pass is bound by its launch and a
 // deep one by its ring and its load too (us per call of one, of two steps, deep against
@@ -483,29 +517,53 @@ int64_t deep_cycles_of(int most, int64_t n) {
 // 1.3 and 2.2 times as fast, equal and equal). So a remainder of one or two after full
 // passes is left to the tiles as well (512^2, eight steps: six and two 22.4, four and
 // four 28.9, tiles 24.4; heated 250^2, eight: 23.0 and 25.1, tiles 25.2; but 400^2 32.4 and
-// 31.4).
+// 31.4; on-node 1501 x 557, six: three and three 63.7, one-cycle passes 60.3), and passes of
+// five are not cut shorter.
+// Three steps of large domains with one on-node axis: 1501 x 557 32.4 deep against 30.2 in
+// one-cycle passes, 1050^2 40.8 / 38.3, with the on-node axis x 44.3 / 41.9, 900^2 35.2 / 39.7.
 int64_t deep_run_cycles(const lbm_ctx *c, int64_t n) {
     const lbm_desc &d = c->dom[0].desc;
     const int64_t nodes = (int64_t)d.nx * d.ny, most = c->deep_cycles;
-    if (on_node_walls(d)) return n < 3 && nodes > 65536 ? 0 : deep_cycles_of((int)most, n);
+    if (most <= 0) return 0;
+    const int64_t rest = n > most ? n % most : 0;
+    if (on_node_walls(d)) {
+        if (n < 3 && nodes > 65536) return 0;
+        if (n == 3 && d.storage == LBM_FP32_DEV &&
+            nodes > (d.bc_x == LBM_PERIODIC ? 700000 : d.bc_y == LBM_PERIODIC ? 1000000 : INT64_MAX))
+            return 0;
+        return (rest == 1 || rest == 2) && nodes > 700000 ? most : deep_cycles_of((int)most, n);
+    }
     const bool small = nodes <= (n == 1 && d.storage == LBM_FP16_DEV ? 65536 : 20000);
     if (n < 3 && !small) return 0;
-    if (n > most && most >= 3 && n % most > 0 && n % most < 3 && nodes > 20000 && (!d.thermal.enabled || nodes <= 65536))
-        return most;
+    const bool heat = d.thermal.enabled != 0, four = four_in_tiles(c);
+    // (heated, where four steps go to tiles, no passes that leave four)
+    const bool to_tiles = heat && nodes > 65536 ? four && (rest == 2 || (rest == 3 && most == 6))
+                                                : rest == 1 || rest == 2;
+    if (nodes > 20000 && (to_tiles || (most == 5 && n > most))) return most;
     return deep_cycles_of((int)most, n);
 }
 
-// And of an lbm_step call with n cycles left: none over a checkpoint. A call of four
-// steps is as fast or faster in two tile passes of two where they fill the chip (400^2
-// 12.4 deep against 11.6, 500^2 channel 13.6 / 12.8, 350^2 10.2 / 11.2; binary16 400^2
-// 11.3 / 12.4, 500^2 13.8 / 12.6; heated 400^2 15.0 / 15.8).
+// And of an lbm_step call with n cycles left: none over a checkpoint. Other calls of a few
+// steps that are as fast or faster in tile passes of one and two cycles (us per call, deep
+// against tiles, one box): three steps in FP32 from 165,000 nodes in uniform and Ergun media
+// (642 x 274 channel 12.0 / 10.9, 450^2 cavity 12.3 / 11.7, 400^2 10.7 / 11.2; 500^2 with a 1/K
+// plane 11.6 / 13.0); where a deep pass holds five cycles four, six and eight (540^2 24.8 / 22.8
+// and 31.7 / 30.2, binary16 24.4 / 21.9 and 28.5 / 29.2, 1000 x 270 29.7 / 27.5). Heated, one
+// tile pass first where seven steps would be four and three (789 x 209 30.1 / 28.7) or eight
+// two fours (binary16 400^2 31.9 / 30.6).
 int64_t deep_pass_cycles(const lbm_ctx *c, int64_t n) {
     const lbm_desc &d = c->dom[0].desc;
+    if (!c->deep_steps) return 0;
     const bool recording = c->rec_valid && d.ckpt_every > 0;
     if (recording) n = std::min<int64_t>(n, d.ckpt_every - c->t % d.ckpt_every);
-    if (n == 4 && c->t > 0 && !recording && !d.thermal.enabled && !on_node_walls(d) &&
-        (int64_t)d.nx * d.ny > (d.storage == LBM_FP16_DEV ? 200000 : 140000))
-        return 0;
+    if (c->deep_cycles > 0 && c->t > 0 && !recording && !on_node_walls(d)) {
+        const int64_t nodes = (int64_t)d.nx * d.ny, most = c->deep_cycles;
+        const bool heat = d.thermal.enabled != 0, half = d.storage == LBM_FP16_DEV;
+        if (n == 4 && four_in_tiles(c)) return 0;
+        if (n == 3 && nodes > 165000 && !heat && !half && medium_kind(c->dom[0].dom) != MK_ANY) return 0;
+        if (most == 5 && (n == 4 || n == 6 || n == 8)) return 0;
+        if (heat && nodes > 65536 && ((most == 6 && n == 7) || (most == 7 && n == 8 && four_in_tiles(c)))) return 0;
+    }
     return deep_run_cycles(c, n);
 }
 
@@ -530,8 +588,9 @@ struct Pass {
 //     1128; cavity 3400^2 258 / 201, 4096^2 325 / 269), in binary16 storage in uniform
 //     media (channel 4096^2 259 / 279, cavity 5800^2 532 / 497);
 //   * rolling passes of three cycles beyond 2,500,000 nodes (1700^2 43 / 44 and 2048^2 channel
-//     77 / 75 in repeated calls, binary16 with a 1/K plane 63 / 60; on a new state, 1221 x
-//     2126, one cycle and three 157 / 146), and with a 1/K or viscosity plane of three
+//     77 / 75 in repeated calls; on a new state, 1221 x 2126, one cycle and three 157 / 146),
+//     in binary16 with planes beyond 2^20 (688 x 2264 27.4 / 26.4, 2048^2 with 1/K 63 / 60),
+//     and with a 1/K or viscosity plane of three
 //     and four beyond 5 x 2^20 (2300^2 115 / 98 and 123 / 115, 2890^2 254 / 159 and 266 /
 //     183); heated ones of three from 2^22 nodes (2100^2 142 / 123);
 //   * isothermal batches whose states that cache does not hold (60 cavities of 64 to 768
@@ -545,7 +604,8 @@ bool short_pass_in_tiles(const lbm_ctx *c, int64_t cycles) {
     const int mk = medium_kind(D.dom);
     if (c->strip) return mk == MK_UNIFORM || (D.desc.storage == LBM_FP32_DEV && nodes >= 6 * M);
     if (D.dom.thermal) return cycles == 3 && nodes >= 4 * M;
-    return cycles == 3 ? nodes > 2500000 : mk == MK_ANY && nodes > 5 * M;
+    const bool half = D.desc.storage == LBM_FP16_DEV;
+    return cycles == 3 ? nodes > (half && mk != MK_UNIFORM ? M : 2500000) : mk == MK_ANY && nodes > 5 * M;
 }
 
 Pass next_pass(const lbm_ctx *c, int64_t n) {
@@ -559,7 +619,12 @@ Pass next_pass(const lbm_ctx *c, int64_t n) {
     if (c->roll || c->strip) {
         const bool any_medium = c->batch ? !c->batch_uniform : medium_kind(D.dom) == MK_ANY;
         const bool thermal = D.dom.thermal != 0;
-        const int k = c->roll ? roll_cycles(thermal, any_medium, n) : strip_cycles(n);
+        int k = c->roll ? roll_cycles(thermal, any_medium, n) : strip_cycles(n);
+        // (heated, six steps on the smallest of these domains: four, and two in a tile pass,
+        // 1038 x 230 in binary16 23.8 us, two of three 26.0, tiles 24.0; 560 x 540 28.5, 28.3
+        // and 29.4)
+        if (thermal && !c->batch && k == 3 && n == 6 && !any_medium &&
+            (int64_t)D.dom.nx * D.dom.ny < 300000) k = 4;
         // (heated, in a medium of any kind, two tile passes of two cycles are faster than
         // a rolling one of three and one more: 1000^2 49 us against 52)
         const bool other = k < (c->roll ? 3 : 4) || (thermal && any_medium && n == 4);
@@ -770,8 +835,9 @@ int lbm_create(const lbm_desc *d, const float *phi, const float *kappa, void *wo
     if (d->storage == LBM_FP16_DEV) c->sched = Schedule{64, 2, 2, 1};
     if (buffer_below_4gib(L)) {
         (void)deep_plan(D.dom, INT64_MAX, &c->deep, &c->deep_cycles);
+        c->deep_steps = c->deep_cycles > 0 && deep_steps_pay(c);
         const int st = d->storage == LBM_FP16_DEV ? ST_F16 : ST_F32;
-        c->roll = c->deep_cycles == 0 && roll_domain(D.dom, st);
+        c->roll = !c->deep_steps && (c->deep_cycles == 0 || d->thermal.enabled) && roll_domain(D.dom, st);
         c->strip = !c->roll && strip_domain(D.dom, st);
     }
     hipError_t e = init_domain(D, 0, phi, kappa, c->stream);

@@ -94,7 +94,8 @@ def test_passes_stop_at_checkpoints(driver):
     (7, "rolling4 rolling3", dict(nx=777, ny=1000, bx=P, medium=KAPPA, j=1)),
     (7, "rolling4 tiles3", dict(nx=2048, ny=2048, bx=P, medium=ERGUN)),
     (3, "tiles3", dict(nx=1221, ny=2126, medium=ERGUN)), (3, "rolling3", dict(nx=1221, ny=2000, medium=ERGUN)),
-    (3, "tiles3", dict(nx=1700, ny=1700, half=1)),
+    (3, "tiles3", dict(nx=1700, ny=1700, half=1)), (3, "tiles3", dict(nx=688, ny=2264, half=1, medium=ERGUN)),
+    (3, "rolling3", dict(nx=1100, ny=1100, half=1)),
     (4, "tiles2 tiles2", dict(nx=1000, ny=1000, heat=1, medium=KAPPA)),
     (7, "rolling3 tiles2 tiles2", dict(nx=1000, ny=1000, heat=1, medium=KAPPA)),
     (7, "rolling4 rolling3", dict(nx=1000, ny=1000, heat=1)), (7, "rolling4 tiles3", dict(nx=2100, ny=2100, heat=1)),
@@ -129,6 +130,23 @@ def test_short_passes_of_large_batches(driver, n, want, kw):
     (2, "tiles2", dict(nx=250, ny=250, heat=1)), (2, "deep2", dict(nx=100, ny=100, heat=1)),
     (2, "deep2", dict(nx=200, ny=200, bx=N, by=N)), (2, "tiles1 tiles1", dict(nx=512, ny=512, bx=N, by=N)),
     (4, "tiles2 tiles2", dict(nx=512, ny=512)), (4, "deep4", dict(nx=300, ny=300)),
+    (3, "tiles2 tiles1", dict(nx=642, ny=274, bx=P, by=P, medium=ERGUN)), (3, "deep3", dict(nx=400, ny=400)),
+    (3, "deep3", dict(nx=500, ny=500, medium=KAPPA)), (3, "deep3", dict(nx=500, ny=500, half=1)),
+    (4, "tiles2 tiles2", dict(nx=317, ny=271, heat=1)), (4, "deep4", dict(nx=250, ny=250, heat=1)),
+    (8, "deep4 deep4", dict(nx=400, ny=400, heat=1)),
+    (6, "tiles2 tiles2 tiles2", dict(nx=540, ny=540)), (10, "rolling4 rolling4 tiles2", dict(nx=450, ny=450, heat=1)),
+    (8, "tiles2 tiles2 tiles2 tiles2", dict(nx=540, ny=540)), (10, "deep5 deep5", dict(nx=540, ny=540)),
+    (12, "deep5 deep5 tiles2", dict(nx=540, ny=540)), (16, "rolling4 rolling4 rolling4 rolling4", dict(nx=600, ny=330, bx=P, medium=ERGUN, heat=1)),
+    (6, "tiles2 tiles2 tiles2", dict(nx=437, ny=577, half=1)), (6, "deep6", dict(nx=520, ny=505, half=1)),
+    (6, "deep5 tiles1", dict(nx=1036, ny=1355, bx=P, by=N, half=1)), (9, "deep7 tiles1 tiles1", dict(nx=980, ny=980, bx=N, by=N)), (9, "deep5 deep4", dict(nx=700, ny=700, bx=N, by=N)),
+    (3, "tiles1 tiles1 tiles1", dict(nx=1501, ny=557, bx=P, by=N)), (3, "deep3", dict(nx=900, ny=900, bx=N, by=P)),
+    (3, "tiles1 tiles1 tiles1", dict(nx=557, ny=1501, bx=P, by=N, heat=1)), (5, "deep5", dict(nx=900, ny=900, bx=P, by=N, heat=1)),
+    (7, "tiles2 deep5", dict(nx=789, ny=209, bx=P, heat=1)), (4, "tiles2 tiles2", dict(nx=400, ny=400, heat=1, half=1)),
+    (8, "tiles2 deep6", dict(nx=400, ny=400, heat=1, half=1)), (14, "deep6 deep6 tiles2", dict(nx=430, ny=430, heat=1, half=1)), (7, "deep7", dict(nx=400, ny=400, heat=1)),
+    (8, "tiles2 deep6", dict(nx=400, ny=400, heat=1, medium=ERGUN)), (9, "deep6 deep3", dict(nx=430, ny=430, heat=1, medium=ERGUN)),
+    (14, "deep5 deep5 deep4", dict(nx=430, ny=430, heat=1)),
+    (6, "rolling4 tiles2", dict(nx=1038, ny=230, heat=1)), (6, "rolling3 rolling3", dict(nx=560, ny=540, heat=1)),
+    (12, "tiles2 tiles2 tiles2 tiles2 tiles2 tiles2", dict(nx=1038, ny=230, heat=1, half=1, medium=KAPPA)),
     (7, "deep6 tiles1", dict(nx=512, ny=512)), (8, "deep6 tiles2", dict(nx=500, ny=500, bx=P, medium=ERGUN)),
     (9, "deep5 tiles2 tiles2", dict(nx=512, ny=512)), (9, "deep9", dict(nx=400, ny=400)),
     (12, "deep6 deep6", dict(nx=512, ny=512)),
