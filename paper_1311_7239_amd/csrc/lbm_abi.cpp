@@ -519,6 +519,9 @@ bool four_in_tiles(const lbm_ctx *c) {
 // four 28.9, tiles 24.4; heated 250^2, eight: 23.0 and 25.1, tiles 25.2; but 400^2 32.4 and
 // 31.4; on-node 1501 x 557, six: three and three 63.7, one-cycle passes 60.3), and passes of
 // five are not cut shorter.
+// On-node walls from 700,000 nodes, equal passes against full ones and the rest in tiles:
+// 900^2, six steps (five and one) 70.0 / 61.8, 980^2, eight (seven and one) 97.2 / 91.5,
+// 491 x 1631, eight (six and two) 71.2 / 68.7; but two in binary16 66.6 / 72.5.
 // Three steps of large domains with one on-node axis: 1501 x 557 32.4 deep against 30.2 in
 // one-cycle passes, 1050^2 40.8 / 38.3, with the on-node axis x 44.3 / 41.9, 900^2 35.2 / 39.7.
 int64_t deep_run_cycles(const lbm_ctx *c, int64_t n) {
@@ -531,7 +534,8 @@ int64_t deep_run_cycles(const lbm_ctx *c, int64_t n) {
         if (n == 3 && d.storage == LBM_FP32_DEV &&
             nodes > (d.bc_x == LBM_PERIODIC ? 700000 : d.bc_y == LBM_PERIODIC ? 1000000 : INT64_MAX))
             return 0;
-        return (rest == 1 || rest == 2) && nodes > 700000 ? most : deep_cycles_of((int)most, n);
+        const bool to_tiles = rest == 1 || (rest == 2 && d.storage == LBM_FP32_DEV);
+        return to_tiles && nodes > 700000 ? most : deep_cycles_of((int)most, n);
     }
     const bool small = nodes <= (n == 1 && d.storage == LBM_FP16_DEV ? 65536 : 20000);
     if (n < 3 && !small) return 0;
@@ -588,9 +592,8 @@ struct Pass {
 //     1128; cavity 3400^2 258 / 201, 4096^2 325 / 269), in binary16 storage in uniform
 //     media (channel 4096^2 259 / 279, cavity 5800^2 532 / 497);
 //   * rolling passes of three cycles beyond 2,500,000 nodes (1700^2 43 / 44 and 2048^2 channel
-//     77 / 75 in repeated calls; on a new state, 1221 x 2126, one cycle and three 157 / 146),
-//     in binary16 with planes beyond 2^20 (688 x 2264 27.4 / 26.4, 2048^2 with 1/K 63 / 60),
-//     and with a 1/K or viscosity plane of three
+//     77 / 75 in repeated calls; on a new state, 1221 x 2126, one cycle and three 157 / 146,
+//     but in binary16 688 x 2264 26.9 / 27.3), and with a 1/K or viscosity plane of three
 //     and four beyond 5 x 2^20 (2300^2 115 / 98 and 123 / 115, 2890^2 254 / 159 and 266 /
 //     183); heated ones of three from 2^22 nodes (2100^2 142 / 123);
 //   * isothermal batches whose states that cache does not hold (60 cavities of 64 to 768
@@ -604,8 +607,7 @@ bool short_pass_in_tiles(const lbm_ctx *c, int64_t cycles) {
     const int mk = medium_kind(D.dom);
     if (c->strip) return mk == MK_UNIFORM || (D.desc.storage == LBM_FP32_DEV && nodes >= 6 * M);
     if (D.dom.thermal) return cycles == 3 && nodes >= 4 * M;
-    const bool half = D.desc.storage == LBM_FP16_DEV;
-    return cycles == 3 ? nodes > (half && mk != MK_UNIFORM ? M : 2500000) : mk == MK_ANY && nodes > 5 * M;
+    return cycles == 3 ? nodes > 2500000 : mk == MK_ANY && nodes > 5 * M;
 }
 
 Pass next_pass(const lbm_ctx *c, int64_t n) {
@@ -627,7 +629,12 @@ Pass next_pass(const lbm_ctx *c, int64_t n) {
             (int64_t)D.dom.nx * D.dom.ny < 300000) k = 4;
         // (heated, in a medium of any kind, two tile passes of two cycles are faster than
         // a rolling one of three and one more: 1000^2 49 us against 52)
-        const bool other = k < (c->roll ? 3 : 4) || (thermal && any_medium && n == 4);
+        // (in binary16 below 300,000 nodes so are they for any even number, 1038 x 230, twelve
+        // steps 52.8 against 57.5; an odd one starts with three rolled, which leaves no tile
+        // pass of one cycle: five steps 23.4 against 32.8)
+        const bool two = thermal && any_medium && !c->batch && n % 2 == 0 && D.desc.storage == LBM_FP16_DEV &&
+                         (int64_t)D.dom.nx * D.dom.ny < 300000;
+        const bool other = k < (c->roll ? 3 : 4) || (thermal && any_medium && n == 4) || two;
         if (!other && (k == 6 || !short_pass_in_tiles(c, k)))
             return Pass{c->roll ? LBM_PASS_ROLLING : LBM_PASS_STRIPS, k};
         if (!other || (c->strip && k == 3)) most = c->batch ? std::min<int64_t>(k, most) : k;

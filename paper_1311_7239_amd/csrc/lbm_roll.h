@@ -393,9 +393,7 @@ int roll_cycles(bool thermal, bool any_medium, int64_t n) {
 //     channel 2240^2 25.7 against 23.6, 2900^2 36.1 against 38.2; convection 2048^2 42
 //     against 35, 3400 x 1500 41 against 49); with a 1/K or a viscosity plane, which
 //     the strip pass does not take, 2900^2 43.2 against 41.7, and heated, in three
-//     cycles, to 2^22 nodes (2100^2, three cycles: 141 against 151) and in binary16
-//     storage from 300,000 (1038 x 230, twelve steps: 55 against 59; 560 x 540 70 against
-//     64);
+//     cycles, to 2^22 nodes (2100^2, three cycles: 141 against 151);
 //   * binary16 storage, whose loads convert, from 400,000 nodes (channel 600^2 3.9
 //     against 4.2, 700^2 4.8 against 4.4; 2048^2 20.7 against 19.6) and in uniform media
 //     to 3 x 2^20 (cavity 1700^2 13.5 against 13.3, 4099 x 1001 16.9 against 18.2).
@@ -405,7 +403,7 @@ bool roll_domain(const Dom &d, int storage) {
     if (d.bc_x == BC_NEE || d.bc_y == BC_NEE || d.nx < 2 * ROLL_COLS || d.ny < ROLL_COLS) return false;
     if (storage == ST_F16 && !d.thermal)
         return mk == MK_UNIFORM ? nodes <= 3 * M : (nodes >= 400000 && nodes <= 4 * M);
-    if (d.thermal) return mk == MK_ANY ? nodes < 4 * M && (storage == ST_F32 || nodes >= 300000) : nodes <= 9 * M / 2;
+    if (d.thermal) return mk == MK_ANY ? nodes < 4 * M : nodes <= 9 * M / 2;
     return nodes <= (mk == MK_ANY ? 8 * M : 5 * M);
 }
 

@@ -94,7 +94,7 @@ def test_passes_stop_at_checkpoints(driver):
     (7, "rolling4 rolling3", dict(nx=777, ny=1000, bx=P, medium=KAPPA, j=1)),
     (7, "rolling4 tiles3", dict(nx=2048, ny=2048, bx=P, medium=ERGUN)),
     (3, "tiles3", dict(nx=1221, ny=2126, medium=ERGUN)), (3, "rolling3", dict(nx=1221, ny=2000, medium=ERGUN)),
-    (3, "tiles3", dict(nx=1700, ny=1700, half=1)), (3, "tiles3", dict(nx=688, ny=2264, half=1, medium=ERGUN)),
+    (3, "tiles3", dict(nx=1700, ny=1700, half=1)), (3, "rolling3", dict(nx=688, ny=2264, half=1, medium=ERGUN)),
     (3, "rolling3", dict(nx=1100, ny=1100, half=1)),
     (4, "tiles2 tiles2", dict(nx=1000, ny=1000, heat=1, medium=KAPPA)),
     (7, "rolling3 tiles2 tiles2", dict(nx=1000, ny=1000, heat=1, medium=KAPPA)),
@@ -147,6 +147,11 @@ def test_short_passes_of_large_batches(driver, n, want, kw):
     (14, "deep5 deep5 deep4", dict(nx=430, ny=430, heat=1)),
     (6, "rolling4 tiles2", dict(nx=1038, ny=230, heat=1)), (6, "rolling3 rolling3", dict(nx=560, ny=540, heat=1)),
     (12, "tiles2 tiles2 tiles2 tiles2 tiles2 tiles2", dict(nx=1038, ny=230, heat=1, half=1, medium=KAPPA)),
+    (7, "deep4 deep3", dict(nx=900, ny=900, bx=N, by=N, half=1)), (6, "deep5 tiles1", dict(nx=900, ny=900, bx=N, by=N, half=1)),
+    (7, "deep5 tiles1 tiles1", dict(nx=900, ny=900, bx=N, by=N)),
+    (5, "rolling3 tiles2", dict(nx=1038, ny=230, heat=1, half=1, medium=KAPPA)),
+    (9, "rolling3 tiles2 tiles2 tiles2", dict(nx=1038, ny=230, heat=1, half=1, medium=KAPPA)),
+    (6, "rolling3 rolling3", dict(nx=560, ny=540, heat=1, half=1, medium=KAPPA)),
     (7, "deep6 tiles1", dict(nx=512, ny=512)), (8, "deep6 tiles2", dict(nx=500, ny=500, bx=P, medium=ERGUN)),
     (9, "deep5 tiles2 tiles2", dict(nx=512, ny=512)), (9, "deep9", dict(nx=400, ny=400)),
     (12, "deep6 deep6", dict(nx=512, ny=512)),
