@@ -327,7 +327,7 @@ int lbm_set_schedule(lbm_ctx *c, int32_t tile_w, int32_t vec, int32_t rows, int3
  * for; EINVAL for another value. */
 int lbm_set_time_blocking(lbm_ctx *c, int32_t cycles_per_pass);
 
-/* Small single domains (up to about 300,000 nodes isothermal, 200,000 with
+/* Small single domains (up to about 300,000 nodes isothermal, 185,000 with
  * the thermal model, about a million with on-node walls) step by deep passes
  * of up to ten cycles per launch, and domains of a few hundred nodes by up to
  * 1024; mid-size ones (up to about five million nodes) by rolling passes of
